@@ -50,6 +50,7 @@ struct sbli_net {
     int wgrad_wg = kWgradWg;
     double* loss_part = nullptr;
     double* loss = nullptr;
+    unsigned* guard_state = nullptr; // [2], zero between guard calls (see closure_guard_kernel)
     int conservative = 0;            // remove each output field's box mean in sbli_net_forward
     double* mean_part = nullptr;     // box-mean partial sums [max_batch * 5][chunks]
     float* mean_val = nullptr;       // box means [max_batch * 5]
@@ -93,7 +94,7 @@ extern "C" int sbli_net_destroy(sbli_net* net) {
     }
     void* ptrs[] = {net->params, net->grads, net->adam_m, net->adam_v, net->stats, net->x, net->h1, net->h2,
                     net->dy, net->d2, net->d1, net->pre1, net->pre2, net->y, net->wpart, net->bpart, net->loss_part,
-                    net->loss, net->mean_part, net->mean_val};
+                    net->loss, net->guard_state, net->mean_part, net->mean_val};
     for (void* p : ptrs) release(p);
     delete net;
     if (first != hipSuccess) return nfail(nullptr, SBLI_ERR_HIP, "sbli_net_destroy: %s", hipGetErrorString(first));
@@ -157,6 +158,7 @@ extern "C" int sbli_net_create(int n, int max_batch, void* hip_stream, sbli_net*
     alloc((void**)&net->bpart, sizeof(float) * (size_t)kBiasWg * 32);
     alloc((void**)&net->loss_part, sizeof(double) * nblk(NP));
     alloc((void**)&net->loss, sizeof(double));
+    alloc((void**)&net->guard_state, 2 * sizeof(unsigned));
     alloc((void**)&net->mean_part, sizeof(double) * (size_t)max_batch * 5 * nblk(net->P, kBoxMeanChunk));
     alloc((void**)&net->mean_val, sizeof(float) * (size_t)max_batch * 5);
     if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
@@ -390,7 +392,8 @@ extern "C" int sbli_net_train_step(sbli_net* net, const float* q, const float* t
 
 extern "C" int sbli_net_guard(sbli_net* net, const float* c, int* flag, unsigned* counters) {
     if (!net || !c || !flag || !counters) return nfail(net, SBLI_ERR_ARG, "sbli_net_guard: NULL argument");
-    closure_guard_kernel<<<1, 1024, 0, net->stream>>>(c, net->P, net->stats + 20, flag, counters);
+    closure_guard_kernel<<<nblk(5 * net->P, kGuardPer), 256, 0, net->stream>>>(c, net->P, net->stats + 20,
+                                                                              net->guard_state, flag, counters);
     NHIP_TRY(net, hipGetLastError());
     return SBLI_OK;
 }

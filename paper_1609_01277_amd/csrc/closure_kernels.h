@@ -633,28 +633,33 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restri
 
 // Closure guard: flag[0] = 1 if every closure value is finite and within
 // +-limit[f] for its field, else 0; counters[0|1] count accepted / rejected.
-__global__ void __launch_bounds__(1024) closure_guard_kernel(const float* __restrict__ C, int64_t P,
-                                                             const float* __restrict__ limit, int* __restrict__ flag,
-                                                             unsigned* __restrict__ counters) {
-    int bad = 0;
-    for (int f = 0; f < 5; ++f) {
-        const float L = limit[f];
-        for (int64_t i = threadIdx.x; i < P; i += blockDim.x) {
-            const float v = C[(int64_t)f * P + i];
-            bad |= !(fabsf(v) <= L);
-        }
-    }
-    __shared__ int sb[1024];
-    sb[threadIdx.x] = bad;
-    __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sb[threadIdx.x] |= sb[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        flag[0] = sb[0] ? 0 : 1;
-        atomicAdd(&counters[sb[0] ? 1 : 0], 1u);
-    }
+// The check reads 5 P values, 5.2 MB at 64^3: the time is that of one pass of
+// loads, so it wants many of them in flight on every CU.  A workgroup checks
+// kGuardPer values; the last one to finish (a ticket counter) writes the verdict
+// and clears `state` for the next call.  At 64^3 one workgroup of 1,024 threads
+// took 368 us, 320 workgroups of 4,096 values take about 5 us.
+// state: {values out of bounds seen, workgroups done}, both 0 before the call.
+constexpr int kGuardPer = 4096;   // divides P (a multiple of 32^3)
+__global__ void __launch_bounds__(256) closure_guard_kernel(const float* __restrict__ C, int64_t P,
+                                                            const float* __restrict__ limit,
+                                                            unsigned* __restrict__ state, int* __restrict__ flag,
+                                                            unsigned* __restrict__ counters) {
+    const float* src = C + (int64_t)blockIdx.x * kGuardPer + threadIdx.x;
+    const float L = limit[(int64_t)blockIdx.x * kGuardPer / P];   // kGuardPer divides P: one field per workgroup
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < kGuardPer / 256; ++k) bad |= !(fabsf(src[256 * k]) <= L);
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x != 0) return;
+    if (any) atomicOr(&state[0], 1u);
+    __threadfence();
+    if (atomicAdd(&state[1], 1u) != gridDim.x - 1) return;
+    // every other workgroup's verdict was published before its ticket
+    __threadfence();
+    const unsigned rejected = atomicExch(&state[0], 0u);
+    atomicExch(&state[1], 0u);
+    flag[0] = rejected ? 0 : 1;
+    atomicAdd(&counters[rejected ? 1 : 0], 1u);
 }
 
 }  // namespace sbli
