@@ -402,6 +402,28 @@ extern "C" int sbli_net_n(const sbli_net* net) { return net ? net->n : SBLI_ERR_
 
 extern "C" void* sbli_net_stream(const sbli_net* net) { return net ? (void*)net->stream : nullptr; }
 
+// The row form where its 16-byte loads are aligned (rows are whole multiples of
+// `ratio` values, so the base decides, except for two FP32 values a load) and the grid
+// fits its launch; every other ratio, alignment and size takes the pointwise form.
+template <typename Tin>
+static void box_filter_launch(hipStream_t s, const Tin* fine, int nf, int nfields, int ratio, float* coarse,
+                              int subtract) {
+    const int nc = nf / ratio;
+    const dim3 grid((nc + 63) / 64, (nc + kFilterWaves - 1) / kFilterWaves,
+                    (unsigned)nfields * ((nc + kFilterZ - 1) / kFilterZ));
+    const bool rows = (uintptr_t)fine % 16 == 0 && grid.y <= 65535 &&
+                      (int64_t)nfields * ((nc + kFilterZ - 1) / kFilterZ) <= 65535;
+    if (rows && ratio == 2)
+        box_filter_rows_kernel<Tin, 2><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract);
+    else if (rows && ratio == 4)
+        box_filter_rows_kernel<Tin, 4><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract);
+    else if (rows && ratio == 8)
+        box_filter_rows_kernel<Tin, 8><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract);
+    else
+        box_filter_kernel<Tin><<<nblk((int64_t)nc * nc * nc * nfields), 256, 0, s>>>(fine, nf, nfields, ratio, coarse,
+                                                                                     subtract);
+}
+
 extern "C" int sbli_box_filter(const void* fine, int dtype, int nf, int nfields, int ratio, float* coarse,
                                int subtract, void* hip_stream) {
     if (!fine || !coarse) return nfail(nullptr, SBLI_ERR_ARG, "sbli_box_filter: NULL pointer");
@@ -409,14 +431,9 @@ extern "C" int sbli_box_filter(const void* fine, int dtype, int nf, int nfields,
         return nfail(nullptr, SBLI_ERR_ARG, "sbli_box_filter: need an even ratio >= 2 dividing nf >= 2 ratio");
     if (dtype != SBLI_F64 && dtype != SBLI_F32) return nfail(nullptr, SBLI_ERR_ARG, "sbli_box_filter: bad dtype");
     const int nc = nf / ratio;
-    const int64_t total = (int64_t)nc * nc * nc * nfields;
     hipStream_t s = (hipStream_t)hip_stream;
-    if (dtype == SBLI_F64)
-        box_filter_kernel<double><<<nblk(total), 256, 0, s>>>((const double*)fine, nf, nfields, ratio, coarse,
-                                                              subtract);
-    else
-        box_filter_kernel<float><<<nblk(total), 256, 0, s>>>((const float*)fine, nf, nfields, ratio, coarse,
-                                                             subtract);
+    if (dtype == SBLI_F64) box_filter_launch(s, (const double*)fine, nf, nfields, ratio, coarse, subtract);
+    else box_filter_launch(s, (const float*)fine, nf, nfields, ratio, coarse, subtract);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return nfail(nullptr, SBLI_ERR_HIP, "sbli_box_filter: %s", hipGetErrorString(e));
     return SBLI_OK;

@@ -66,6 +66,88 @@ __global__ void __launch_bounds__(256) box_filter_kernel(const Tin* __restrict__
     coarse[o] = subtract ? (float)(acc - (double)coarse[o]) : (float)acc;
 }
 
+// The same filter for ratio 2, 4 and 8 on 16-byte aligned rows.  The filter reads
+// every fine value about once (1.25^2 times with ratio 4's shared end rows), so its
+// time should be that of one pass over the fine fields; one thread per output point
+// reading its (ratio + 1)^3 values one by one took 316 us for five 256^3 FP64 fields
+// (671 MB), most of it in strided loads.  Here a lane loads the `ratio` consecutive
+// values from its own point on (16-byte loads, a wavefront covers one contiguous run
+// of a row) and takes the ratio/2 values to its left from the lane below; a thread
+// marches kFilterZ output planes, and the z-plane two outputs share is reduced once.
+// About 175 us.  The sums run in the order of box_filter_kernel, so the results are the
+// same bits.
+constexpr int kFilterZ = 4;      // output planes of a workgroup: 4 ratio + 1 fine planes
+constexpr int kFilterWaves = 4;  // output rows of a workgroup
+template <typename Tin, int RATIO>
+__global__ void __launch_bounds__(64 * kFilterWaves)
+    box_filter_rows_kernel(const Tin* __restrict__ fine, int nf, float* __restrict__ coarse, int subtract) {
+    constexpr int H = RATIO / 2;
+    constexpr int VL = 16 / (int)sizeof(Tin) < RATIO ? 16 / (int)sizeof(Tin) : RATIO;   // values of one load
+    typedef Tin Vec __attribute__((ext_vector_type(VL)));
+    const int nc = nf / RATIO;
+    const int64_t Pc = (int64_t)nc * nc * nc, Pf = (int64_t)nf * nf * nf;
+    const int lane = threadIdx.x & 63;
+    const int xc = blockIdx.x * 64 + lane;
+    const int yc = blockIdx.y * kFilterWaves + (threadIdx.x >> 6);
+    const int nzb = (nc + kFilterZ - 1) / kFilterZ;
+    const int f = blockIdx.z / nzb, zc0 = (blockIdx.z % nzb) * kFilterZ;
+    if (yc >= nc) return;                              // a whole wavefront
+    const int xl = xc < nc ? xc : nc - 1;              // lanes beyond the row repeat its last point
+    const double wi = 1.0 / RATIO, we = 0.5 / RATIO;
+    const Tin* src = fine + (int64_t)f * Pf;
+    // x sum of fine row `row` at this lane's output point
+    auto xsum = [&](const Tin* row) {
+        Tin v[RATIO];
+#pragma unroll
+        for (int k = 0; k < RATIO; k += VL) {
+            const Vec t = *(const Vec*)(row + xl * RATIO + k);
+#pragma unroll
+            for (int e = 0; e < VL; ++e) v[k + e] = t[e];
+        }
+        Tin left[H];
+#pragma unroll
+        for (int k = 0; k < H; ++k) left[k] = __shfl_up(v[RATIO - H + k], 1);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < H; ++k) left[k] = row[wrapn(xl * RATIO - H + k, nf)];
+        }
+        double acc = 0.0;
+#pragma unroll
+        for (int dx = -H; dx <= H; ++dx) {
+            const double wx = (dx == -H || dx == H) ? we : wi;
+            acc += wx * (double)(dx < 0 ? left[dx + H < 0 ? 0 : (dx + H < H ? dx + H : 0)] : v[dx < 0 ? 0 : dx]);
+        }
+        return acc;
+    };
+    // y sum of the x sums at fine plane z
+    auto ysum = [&](int z) {
+        const Tin* pz = src + (int64_t)wrapn(z, nf) * nf * nf;
+        double acc = 0.0;
+#pragma unroll
+        for (int dy = -H; dy <= H; ++dy) {
+            const double wy = (dy == -H || dy == H) ? we : wi;
+            acc += wy * xsum(pz + (int64_t)wrapn(yc * RATIO + dy, nf) * nf);
+        }
+        return acc;
+    };
+    const int zc1 = min(zc0 + kFilterZ, nc);
+    double shared_plane = ysum(zc0 * RATIO - H);       // the plane this output shares with the one below
+    for (int zc = zc0; zc < zc1; ++zc) {
+        double acc = 0.0;
+        acc += we * shared_plane;
+#pragma unroll
+        for (int dz = -H + 1; dz <= H; ++dz) {
+            const double s = ysum(zc * RATIO + dz);
+            acc += (dz == H ? we : wi) * s;
+            if (dz == H) shared_plane = s;
+        }
+        if (xc < nc) {
+            const int64_t o = (int64_t)f * Pc + ((int64_t)zc * nc + yc) * nc + xc;
+            coarse[o] = subtract ? (float)(acc - (double)coarse[o]) : (float)acc;
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Per-channel mean, standard deviation (population statistics, FP64 sums) and
 // largest magnitude of `count` planar [5][P] FP32 arrays.  One block per channel.

@@ -1,8 +1,12 @@
-"""Edges of the many-workgroup closure guard."""
+"""Edges of the box filter's row form and of the many-workgroup closure guard."""
 import numpy as np
 import pytest
 
+import synth
+from oracle import nn
+
 pytestmark = pytest.mark.gpu
+U = 2.0 ** -24   # unit roundoff of the FP32 output
 
 
 def _mods():
@@ -11,6 +15,36 @@ def _mods():
         pytest.fail("GPU test run without a HIP device")
     from paper_1609_01277_amd import closure
     return closure, torch
+
+
+# nc = nf / ratio: below, at and beyond a 64-lane row; rows and planes left over by a workgroup's
+# 4 x 4; ratio 6 and an odd element offset take the pointwise form
+@pytest.mark.parametrize("nf,ratio,offset", [(4, 2, 0), (34, 2, 0), (128, 2, 0), (130, 2, 0), (12, 4, 0), (76, 4, 0),
+                                             (260, 4, 0), (16, 8, 0), (72, 8, 0), (36, 6, 0), (76, 4, 1)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_box_filter_edges_match_oracle(nf, ratio, offset, dtype):
+    closure, torch = _mods()
+    nfields = 5 if nf < 200 else 1
+    f = synth.random_conservative_state(nf, seed=nf + ratio)[:nfields]
+    t = torch.float64 if dtype == "f64" else torch.float32
+    buf = torch.empty(nfields * nf ** 3 + offset, dtype=t, device="cuda")
+    fine = buf[offset:].view(nfields, nf, nf, nf)
+    fine.copy_(torch.from_numpy(np.ascontiguousarray(f)))
+    nc = nf // ratio
+    src = fine.cpu().numpy().astype(np.float64)
+    ref = nn.box_filter(src, ratio)
+    # FP64 sums of (ratio + 1)^3 weighted values, three nested sums: below 4 (ratio + 3) 2^-53 of the
+    # largest value; then one rounding to FP32
+    tol = U * np.abs(ref) + 4 * (ratio + 3) * 2.0 ** -53 * np.abs(src).max()
+    out = torch.empty((nfields, nc, nc, nc), dtype=torch.float32, device="cuda")
+    closure.sbli_box_filter(fine, nf, nfields, ratio, out)
+    assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - ref) <= tol)
+    c0 = np.random.default_rng(nf).standard_normal(ref.shape).astype(np.float32)
+    out = torch.from_numpy(c0).cuda()
+    closure.sbli_box_filter(fine, nf, nfields, ratio, out, subtract=True)
+    got = out.cpu().numpy().astype(np.float64)
+    want = ref - c0.astype(np.float64)
+    assert np.all(np.abs(got - want) <= U * np.abs(want) + 4 * (ratio + 4) * 2.0 ** -53 * (np.abs(src).max() + 5.0))
 
 
 @pytest.mark.parametrize("n", [32, 64])
