@@ -3,14 +3,14 @@
 // 2..12 (the fused stage kernel's register window and LDS planes do not fit
 // beyond order 8) and is a launch variant of the lower orders as well, where it
 // reproduces the fused kernel bit for bit: both compute the same per-point
-// arithmetic in the same order (make_pf, the gradient sums, DirSums::add /
-// finish, the 2N update).  The point fields (u_i, p, T) are recomputed by
+// arithmetic in the same order (make_pf, the gradient sums, nested_terms,
+// ResidualSums, the 2N update).  The point fields (u_i, ei, T) are recomputed by
 // make_pf from q wherever a point is read; the same function of the same inputs,
 // they are the values the fused kernel keeps in its window.
 //
-//   1. staged_nested_zring_kernel: nf = (V_0, V_1, V_2, theta - g_00,
-//      theta - g_11, theta - g_22) with g_ij = D_j u_i, V_j = u_i tau_ij (paper
-//      Sec. "Expanding": the inner derivative of a nested term is taken first);
+//   1. staged_nested_zring_kernel: nf = (V_0, V_1, V_2, t_0, t_1, t_2), the
+//      velocity parts of the nested terms (nested_terms; paper Sec. "Expanding":
+//      the inner derivative of a nested term is taken first);
 //   2. staged_tiled_kernel:  the residual (paper eqs. of mass, momentum and
 //      energy in the skew-symmetric form) from q and nf at the 2R neighbours
 //      along each axis, then the 2N Runge-Kutta update.
@@ -40,15 +40,18 @@ namespace sbli {
 // of TS + 2R points) for the x sums, then the tile with its y arms (TS + 2R rows of
 // TS points) in the same LDS for the y sums.  Each thread keeps its own point in
 // registers and writes it into both strips; only the arms are loaded by the
-// workgroup.  A strip holds the ten point fields and the nested pair of its axis,
-// which keeps a workgroup's LDS small enough that registers, not LDS, bound the
+// workgroup.  A strip holds the point fields a stencil reads and the nested pair of its
+// axis, which keeps a workgroup's LDS small enough that registers, not LDS, bound the
 // number of workgroups per CU up to order 12.
 constexpr int kStagedTile = 16;
 // Planes per run of the z-marching nested-field step (2R planes of the own
 // column are loaded ahead of each run).  Runs of 32 and 128 measure the same at
 // 512^3, orders 8 and 12.
 constexpr int kNestedRun = 64;
-constexpr int kStagedFields = 12;   // rho, rho u_i, rho E, u_i, p, T, then V_d, theta - g_dd of the axis d
+// Fields of a strip: rho, rho E, Th, u_i, then W_d, G_d of the strip's axis d (see
+// nested_terms), then the momentum where LDS keeps it (kMomentumInLds).
+template <typename T, bool PL>
+constexpr int kStagedFields = (kMomentumInLds<T> ? 11 : 8) + (PL ? 1 : 0);   // and p where W, G have none of it
 
 // The unit of work of a tiled launch is (tile, run of zc planes).  Units are
 // numbered by pairs of x-adjacent tiles, plane run by plane run within a pair
@@ -89,7 +92,8 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
                         const T* __restrict__ clos, const int* __restrict__ cflag, int tiles_x, int tiles_y,
                         int zchunk) {
     constexpr int TS = kStagedTile, SW = TS + 2 * R, NT = TS * TS, NA = 2 * R * TS;
-    __shared__ T sb[kStagedFields][TS * SW];
+    constexpr bool PL = kPlain<T, MODE>;
+    __shared__ T sb[kStagedFields<T, PL>][TS * SW];
     const int nx = c.n[0], ny = c.n[1], nz = c.n[2];
     const int64_t P = c.P, plane = (int64_t)nx * ny;
     int tile, chunk;
@@ -104,86 +108,98 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
     unsigned fxo, fyo;
     const int64_t col = (int64_t)fold_index(y0 + cy, ny, c.sym[1], fyo) * nx + fold_index(x0 + cx, nx, c.sym[0], fxo);
     auto point_at = [&](int64_t ix) {
-        return make_pf<T>(q[ix], q[P + ix], q[2 * P + ix], q[3 * P + ix], q[4 * P + ix], c.gm1, c.gM2);
+        return make_pf<T, PL>(q[ix], q[P + ix], q[2 * P + ix], q[3 * P + ix], q[4 * P + ix], c);
     };
     auto lds_point = [&](int i) {
         PF<T> p;
         p.rho = sb[0][i];
-        p.m0 = sb[1][i];
-        p.m1 = sb[2][i];
-        p.m2 = sb[3][i];
-        p.E = sb[4][i];
-        p.u0 = sb[5][i];
-        p.u1 = sb[6][i];
-        p.u2 = sb[7][i];
-        p.p = sb[8][i];
-        p.Tm = sb[9][i];
+        p.E = sb[1][i];
+        p.ei = 0;
+        if constexpr (PL) p.ei = sb[kStagedFields<T, PL> - 1][i];
+        p.Th = sb[2][i];
+        p.u0 = sb[3][i];
+        p.u1 = sb[4][i];
+        p.u2 = sb[5][i];
+        if constexpr (kMomentumInLds<T>) {
+            p.m0 = sb[8][i];
+            p.m1 = sb[9][i];
+            p.m2 = sb[10][i];
+        } else {
+            p.m0 = p.rho * p.u0;
+            p.m1 = p.rho * p.u1;
+            p.m2 = p.rho * p.u2;
+        }
         return p;
     };
     // a point mirrored across x (fx) and/or y (fy), and the nested pair of the strip
-    auto put = [&](int i, const PF<T>& p, unsigned fx, unsigned fy, T v, T th) {
+    auto put = [&](int i, const PF<T>& p, unsigned fx, unsigned fy, T W, T G) {
         sb[0][i] = p.rho;
-        sb[1][i] = flip_sign(p.m0, fx);
-        sb[2][i] = flip_sign(p.m1, fy);
-        sb[3][i] = p.m2;
-        sb[4][i] = p.E;
-        sb[5][i] = flip_sign(p.u0, fx);
-        sb[6][i] = flip_sign(p.u1, fy);
-        sb[7][i] = p.u2;
-        sb[8][i] = p.p;
-        sb[9][i] = p.Tm;
-        sb[10][i] = v;
-        sb[11][i] = th;
+        sb[1][i] = p.E;
+        sb[2][i] = p.Th;
+        sb[3][i] = flip_sign(p.u0, fx);
+        sb[4][i] = flip_sign(p.u1, fy);
+        sb[5][i] = p.u2;
+        sb[6][i] = W;
+        sb[7][i] = G;
+        if constexpr (kMomentumInLds<T>) {
+            sb[8][i] = flip_sign(p.m0, fx);
+            sb[9][i] = flip_sign(p.m1, fy);
+            sb[10][i] = p.m2;
+        }
+        if constexpr (PL) sb[kStagedFields<T, PL> - 1][i] = p.ei;
     };
     for (int z = z0; z < z1; ++z) {
         const int64_t pz = (int64_t)z * plane, id = pz + col;
         const PF<T> s = point_at(id);
-        T Rr = 0, R0 = 0, R1 = 0, R2 = 0, RE = 0;
+        auto W_of = [&](T V, const PF<T>& p, T u) { return nested_W<PL>(V, p.ei, u, c); };
+        auto G_of = [&](T t, const PF<T>& p) { return nested_G<PL>(t, p.ei, c); };
+        const PF<T> sxy = centre_xy(s);
+        ResidualSums<T, PL> rs;
+        rs.start(s, c);
         __syncthreads();   // the previous plane's y-strip reads are done
-        put(cy * SW + R + cx, s, fxo, fyo, flip_sign(nf[id], fxo), nf[3 * P + id]);   // V_x: odd under an x mirror
+        put(cy * SW + R + cx, s, fxo, fyo, flip_sign(W_of(nf[id], s, s.u0), fxo), G_of(nf[3 * P + id], s));   // W_x: odd under an x mirror
         for (int e = tid; e < NA; e += NT) {
             const int side = e / (R * TS), r = e % (R * TS);
             const int ly = r / R, lx = side ? R + TS + r % R : r % R;
             unsigned fx, fy;
             const int64_t ix = pz + (int64_t)fold_index(y0 + ly, ny, c.sym[1], fy) * nx +
                                fold_index(x0 - R + lx, nx, c.sym[0], fx);
-            put(ly * SW + lx, point_at(ix), fx, fy, flip_sign(nf[ix], fx), nf[3 * P + ix]);
+            const PF<T> p = point_at(ix);
+            put(ly * SW + lx, p, fx, fy, flip_sign(W_of(nf[ix], p, p.u0), fx), G_of(nf[3 * P + ix], p));
         }
         __syncthreads();
         {
             const int i = cy * SW + R + cx;
-            DirSums<T> ds;
-            ds.zero();
+            rs.begin();
 #pragma unroll 1
             for (int m = 1; m <= R; ++m)
-                ds.template add<0>(lds_point(i + m), sb[10][i + m], sb[11][i + m], lds_point(i - m), sb[10][i - m],
-                                   sb[11][i - m], c.da[0][m - 1], c.d2c[0][m - 1]);
-            ds.template finish<0>(s, c.d2c0[0], c, Rr, R0, R1, R2, RE);
+                rs.template add<0>(sxy, lds_point(i + m), sb[6][i + m], sb[7][i + m], lds_point(i - m), sb[6][i - m],
+                                   sb[7][i - m], c, m - 1);
+            rs.template end<0>(sxy, c);
         }
         __syncthreads();   // the x-strip reads are done
-        put((R + cy) * TS + cx, s, fxo, fyo, flip_sign(nf[P + id], fyo), nf[4 * P + id]);   // V_y: odd under a y mirror
+        put((R + cy) * TS + cx, s, fxo, fyo, flip_sign(W_of(nf[P + id], s, s.u1), fyo), G_of(nf[4 * P + id], s));   // W_y: odd under a y mirror
         for (int e = tid; e < NA; e += NT) {
             const int side = e / (R * TS), r = e % (R * TS);
             const int lx = r % TS, ly = side ? R + TS + r / TS : r / TS;
             unsigned fx, fy;
             const int64_t ix = pz + (int64_t)fold_index(y0 - R + ly, ny, c.sym[1], fy) * nx +
                                fold_index(x0 + lx, nx, c.sym[0], fx);
-            put(ly * TS + lx, point_at(ix), fx, fy, flip_sign(nf[P + ix], fy), nf[4 * P + ix]);
+            const PF<T> p = point_at(ix);
+            put(ly * TS + lx, p, fx, fy, flip_sign(W_of(nf[P + ix], p, p.u1), fy), G_of(nf[4 * P + ix], p));
         }
         __syncthreads();
         {
             const int i = (R + cy) * TS + cx;
-            DirSums<T> ds;
-            ds.zero();
+            rs.begin();
 #pragma unroll 1
             for (int m = 1; m <= R; ++m)
-                ds.template add<1>(lds_point(i + m * TS), sb[10][i + m * TS], sb[11][i + m * TS], lds_point(i - m * TS),
-                                   sb[10][i - m * TS], sb[11][i - m * TS], c.da[1][m - 1], c.d2c[1][m - 1]);
-            ds.template finish<1>(s, c.d2c0[1], c, Rr, R0, R1, R2, RE);
+                rs.template add<1>(sxy, lds_point(i + m * TS), sb[6][i + m * TS], sb[7][i + m * TS], lds_point(i - m * TS),
+                                   sb[6][i - m * TS], sb[7][i - m * TS], c, m - 1);
+            rs.template end<1>(sxy, c);
         }
         {
-            DirSums<T> ds;
-            ds.zero();
+            rs.begin();
 #pragma unroll 1
             for (int m = 1; m <= R; ++m) {
                 unsigned fa, fb;
@@ -194,15 +210,17 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
                 a.u2 = flip_sign(a.u2, fa);
                 b.m2 = flip_sign(b.m2, fb);
                 b.u2 = flip_sign(b.u2, fb);
-                ds.template add<2>(a, flip_sign(nf[2 * P + ia], fa), nf[5 * P + ia], b, flip_sign(nf[2 * P + ib], fb),
-                                   nf[5 * P + ib], c.da[2][m - 1], c.d2c[2][m - 1]);
+                // (a's and b's velocity and V change sign together, and so does W)
+                rs.template add<2>(s, a, W_of(flip_sign(nf[2 * P + ia], fa), a, a.u2), G_of(nf[5 * P + ia], a), b,
+                                   W_of(flip_sign(nf[2 * P + ib], fb), b, b.u2), G_of(nf[5 * P + ib], b), c, m - 1);
             }
-            ds.template finish<2>(s, c.d2c0[2], c, Rr, R0, R1, R2, RE);
+            rs.template end<2>(s, c);
         }
         if (store) {
             // dq and the new state are streamed (nothing in this launch reads them
             // again), which leaves L2 to the z neighbours and arms of the tiles
-            T Rv[5] = {Rr, R0, R1, R2, RE};
+            T Rv[5];
+            rs.result(Rv);
             if (clos != nullptr && cflag[0] != 0) {
 #pragma unroll
                 for (int f = 0; f < 5; ++f) Rv[f] += clos[f * P + id];
@@ -233,7 +251,7 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
 // values the fused kernel's gradient step reads), and the sums over m run in
 // ascending order per component and axis, as there.  LDS is double-buffered:
 // one barrier per plane.
-template <typename T, int R, int TS>
+template <typename T, int R, int TS, bool PL>
 __global__ void __launch_bounds__(TS * TS)
     staged_nested_zring_kernel(const T* __restrict__ q, T* __restrict__ nf, const BoxConst<T> c, int tiles_x,
                                int tiles_y, int zchunk) {
@@ -355,18 +373,12 @@ __global__ void __launch_bounds__(TS * TS)
         }
         if (store) {
             const int64_t id = (int64_t)z * plane + col;
-            const T theta = g[0][0] + g[1][1] + g[2][2];
+            T V[3], t[3];
+            nested_terms<PL>(g, uc[0], uc[1], uc[2], c, V, t);
 #pragma unroll
             for (int jj = 0; jj < 3; ++jj) {
-                T v = 0;
-#pragma unroll
-                for (int ii = 0; ii < 3; ++ii) {
-                    T tau = c.inv_Re * (g[ii][jj] + g[jj][ii]);
-                    if (ii == jj) tau = fmaT(-c.inv_Re23, theta, tau);
-                    v = fmaT(uc[ii], tau, v);
-                }
-                __builtin_nontemporal_store(v, &nf[jj * P + id]);
-                __builtin_nontemporal_store(theta - g[jj][jj], &nf[(3 + jj) * P + id]);
+                __builtin_nontemporal_store(V[jj], &nf[jj * P + id]);
+                __builtin_nontemporal_store(t[jj], &nf[(3 + jj) * P + id]);
             }
         } else {
             // as many (dropped) stores, so that waiting for the next plane's loads

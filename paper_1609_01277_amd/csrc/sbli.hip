@@ -69,18 +69,35 @@ static void fill_const(const sbli_ctx* x, BoxConst<T>& c) {
     c.n[1] = x->p.ny;
     c.n[2] = x->p.nz;
     c.P = (int64_t)x->p.nx * x->p.ny * x->p.nz;
-    for (int d = 0; d < 3; ++d) {
+    const double inv_Re = 1.0 / x->p.Re, inv_3Re = 1.0 / (3.0 * x->p.Re);
+    for (int d = 0; d < 3; ++d)
         for (int m = 0; m < kMaxR; ++m) {
-            c.da[d][m] = (T)(m < x->r ? x->a[m] / x->h[d] : 0.0);
-            c.d2c[d][m] = (T)(m < x->r ? x->c[m] / (x->h[d] * x->h[d]) : 0.0);
+            const double a = m < x->r ? x->a[m] / x->h[d] : 0.0;
+            const double c2 = m < x->r ? x->c[m] / (x->h[d] * x->h[d]) : 0.0;
+            c.da[d][m] = (T)a;
+            c.v2[d][m] = (T)(-2.0 * c2 * inv_Re);
+            c.v2n[d][m] = (T)(-2.0 * c2 * (inv_Re + inv_3Re));
         }
+    // the centre weight cancels the pair weights as they are stored (c_0 = -2 sum c_m)
+    for (int i = 0; i < 3; ++i) {
+        double sum = 0.0;
+        for (int d = 0; d < 3; ++d)
+            for (int m = 0; m < x->r; ++m) sum += (double)(d == i ? c.v2n[d][m] : c.v2[d][m]);
+        c.v0[i] = (T)(-2.0 * sum);
+    }
+    c.gm1x2 = (T)(2.0 * (x->p.gamma - 1.0));
+    c.gPr = (T)(x->p.gamma / x->p.Pr);
+    c.inv_Re2 = (T)(2.0 * inv_Re);
+    c.inv_3Re2 = (T)(2.0 * inv_3Re);
+    for (int d = 0; d < 3; ++d) {
+        for (int m = 0; m < kMaxR; ++m) c.d2c[d][m] = (T)(m < x->r ? x->c[m] / (x->h[d] * x->h[d]) : 0.0);
         c.d2c0[d] = (T)(x->c0 / (x->h[d] * x->h[d]));
     }
     const double g = x->p.gamma, M = x->p.Mach;
     c.gm1 = (T)(g - 1.0);
     c.gM2 = (T)(g * M * M);
-    c.inv_Re = (T)(1.0 / x->p.Re);
-    c.inv_3Re = (T)(1.0 / (3.0 * x->p.Re));
+    c.inv_Re = (T)inv_Re;
+    c.inv_3Re = (T)inv_3Re;
     c.inv_Re23 = (T)(2.0 / (3.0 * x->p.Re));
     c.kappa = (T)(1.0 / ((g - 1.0) * M * M * x->p.Pr * x->p.Re));
     for (int d = 0; d < 3; ++d) c.sym[d] = x->p.bc[d] == SBLI_BC_SYMMETRY;

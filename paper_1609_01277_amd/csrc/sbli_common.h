@@ -10,12 +10,21 @@ constexpr int kMaxR = 6;   // largest supported stencil radius (order 12)
 
 // Constants of one periodic box, pre-scaled so the kernels never divide by the
 // grid spacing (paper Sec. "Code generation": rationals and reciprocals such as
-// 1/Re are evaluated once and stored).
+// 1/Re are evaluated once and stored).  The residual is summed as -2 dq/dt (see
+// ResidualSums); its weights carry the coefficients and that factor.
 template <typename T>
 struct BoxConst {
     int n[3];                 // points per axis (x, y, z)
     int64_t P;                // n0 * n1 * n2
-    T da[3][kMaxR];           // a_m / h_axis         (first derivative)
+    T da[3][kMaxR];           // a_m / h_axis                            (first derivative)
+    T v2[3][kMaxR];           // -2 c_m / (h_axis^2 Re)                  (viscous Laplacian, heat flux)
+    T v2n[3][kMaxR];          // 4/3 of it: velocity normal to the axis, with its part of grad div u
+    T v0[3];                  // centre weight of the viscous terms of velocity component i, all axes
+    T gm1x2;                  // 2 (gamma - 1)
+    T gPr;                    // gamma / Pr
+    T inv_Re2;                // 2 / Re
+    T inv_3Re2;               // 2 / (3 Re)
+    // constants of the plain sums (FP32 residual, see kPlain)
     T d2c0[3];                // c_0 / h_axis^2       (second derivative)
     T d2c[3][kMaxR];          // c_m / h_axis^2
     T gm1;                    // gamma - 1

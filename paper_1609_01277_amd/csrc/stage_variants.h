@@ -13,27 +13,26 @@ namespace sbli {
 struct StageVariant {
     int tx, ty, pre, rot;
     int minw;   // wavefronts per SIMD the register allocation must allow (1 = as many VGPRs as needed)
-    int db;     // 1: double-buffered LDS planes, one barrier per z-iteration
+    int db;     // barrier schedule: 0 two barriers a plane, 1 one, 2 one and the work split between
+                // column and plane wavefronts (kernels_stage_fused.h)
     int zl;     // 1: the R planes below the output plane in LDS instead of registers
 };
 
-// X-macro lists of (TX, TY, PRE, RT, MINW, DB, ZL) per (type, radius).  The first
-// entry is the default before tuning.
+// X-macro lists of (TX, TY, PRE, RT, MINW, DB, ZL) per (type, radius).
 #define SBLI_VARIANTS_D1(X) \
-    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0) X(16, 16, 1, 1, 1, 1, 0)
-#define SBLI_VARIANTS_D2(X)                                                                                    \
-    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(16, 16, 0, 1, 1, 0, 0) X(32, 8, 0, 0, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0) \
-    X(16, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 0, 1, 1, 0)
+    X(16, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0)
+#define SBLI_VARIANTS_D2(X) \
+    X(16, 16, 1, 1, 1, 2, 0) X(16, 8, 1, 1, 2, 2, 0) X(16, 16, 1, 1, 1, 1, 0) X(16, 8, 1, 1, 2, 0, 0)
 #define SBLI_VARIANTS_D3(X) X(8, 8, 0, 0, 1, 0, 0) X(8, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 1, 0)
 #define SBLI_VARIANTS_D4(X) \
     X(16, 4, 0, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 0) X(8, 8, 0, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 1) X(8, 8, 1, 0, 1, 0, 1)
 #define SBLI_VARIANTS_F1(X) \
     X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 1, 0)
-#define SBLI_VARIANTS_F2(X)                                                                                   \
-    X(16, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 1, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 3, 0, 0) \
-    X(16, 16, 1, 1, 3, 0, 0) X(16, 16, 1, 1, 1, 1, 0) X(32, 8, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 3, 1, 0)            \
-    X(32, 16, 1, 1, 1, 0, 0) X(32, 16, 1, 1, 1, 1, 0)
-#define SBLI_VARIANTS_F3(X) X(16, 16, 0, 0, 1, 0, 0) X(16, 16, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0)
+#define SBLI_VARIANTS_F2(X)                                                                                 \
+    X(32, 16, 1, 1, 1, 1, 0) X(32, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 1, 1, 0)            \
+    X(16, 16, 1, 1, 1, 2, 0) X(16, 8, 1, 1, 1, 0, 0)
+#define SBLI_VARIANTS_F3(X) \
+    X(16, 16, 0, 0, 1, 0, 0) X(16, 16, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 2, 0)
 #define SBLI_VARIANTS_F4(X) X(16, 8, 0, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 0)
 
 // One launch: the boxes (device table), their total workgroup count, the mode
@@ -50,13 +49,12 @@ struct StageArgs {
 
 template <typename T, int R, int TX, int TY, int PRE, int RT, int MINW, int DB, int ZL, int MODE>
 inline void launch_fused_cfg(const StageArgs& a, const T* qin, T* dq, T* qout) {
+    constexpr int nt = fused_threads<R, TX, TY, DB>();
     if (a.sym)
-        fused_stage_kernel<T, R, TX, TY, MODE, PRE, RT, MINW, 1, DB, ZL><<<dim3(a.total_wg), FusedShape<R, TX, TY>::NT,
-                                                                       0, a.stream>>>(
+        fused_stage_kernel<T, R, TX, TY, MODE, PRE, RT, MINW, 1, DB, ZL><<<dim3(a.total_wg), nt, 0, a.stream>>>(
             qin, dq, qout, (const BoxInst<T>*)a.inst, a.ninst, (T)a.dt_scale, (T)a.A, (T)a.B);
     else
-        fused_stage_kernel<T, R, TX, TY, MODE, PRE, RT, MINW, 0, DB, ZL><<<dim3(a.total_wg), FusedShape<R, TX, TY>::NT,
-                                                                       0, a.stream>>>(
+        fused_stage_kernel<T, R, TX, TY, MODE, PRE, RT, MINW, 0, DB, ZL><<<dim3(a.total_wg), nt, 0, a.stream>>>(
             qin, dq, qout, (const BoxInst<T>*)a.inst, a.ninst, (T)a.dt_scale, (T)a.A, (T)a.B);
 }
 

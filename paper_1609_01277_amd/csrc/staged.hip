@@ -19,7 +19,12 @@ static void staged_run(const StagedArgs& a, const T* qin, T* dq, T* qout, T* nf)
         constexpr int TN = (sizeof(T) == 8 && R > 4) ? kStagedTile : 2 * kStagedTile;
         const int tx = (c.n[0] + TN - 1) / TN, ty = (c.n[1] + TN - 1) / TN;
         const int zn = kNestedRun;
-        staged_nested_zring_kernel<T, R, TN><<<grid_of(tx * ty, zn), TN * TN, 0, a.stream>>>(qin, nf, c, tx, ty, zn);
+        if (sizeof(T) == 4 && a.mode == kModeRHS)   // kPlain
+            staged_nested_zring_kernel<T, R, TN, kPlain<T, kModeRHS>><<<grid_of(tx * ty, zn), TN * TN, 0, a.stream>>>(
+                qin, nf, c, tx, ty, zn);
+        else
+            staged_nested_zring_kernel<T, R, TN, false><<<grid_of(tx * ty, zn), TN * TN, 0, a.stream>>>(qin, nf, c, tx,
+                                                                                                         ty, zn);
     }
     const int tx = (c.n[0] + kStagedTile - 1) / kStagedTile, ty = (c.n[1] + kStagedTile - 1) / kStagedTile;
     constexpr int NT = kStagedTile * kStagedTile;
