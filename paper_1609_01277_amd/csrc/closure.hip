@@ -1,6 +1,7 @@
 // libsbli: host side of the learned closure (include/sbli_closure.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -21,7 +22,7 @@ constexpr int kCpad[4] = {8, 32, 32, 8};    // padded channel strides of the act
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-constexpr int kWgradWg = 512;   // workgroups of the weight-gradient kernel (fixed, so the sum order is fixed)
+constexpr int kWgradWg = 512;   // most workgroups of the weight-gradient kernel (a fixed share each, so the sum order is fixed)
 
 struct Layer {
     int cin, cout, cpad, opad;   // real and padded input / output channels
@@ -284,10 +285,22 @@ static void conv(sbli_net* net, const __bf16* in, int cpad, const __bf16* W, int
 // reductions into dW (master layout) and db.
 static void wgrad_launch(hipStream_t stream, int n, int batch, const __bf16* in, int cpad, int cin, const __bf16* dout,
                          int opad, int cout, int nwg, float* wpart, float* bpart, float* dW, float* db) {
-    const int Kpad32 = round_up(27 * cpad, 32);
-    const int64_t blocks = (int64_t)batch * n * n * (n / 32);
-    conv_wgrad_kernel<<<nwg, 256, 0, stream>>>(in, cpad, dout, opad, n, blocks, Kpad32, wpart);
-    wgrad_reduce_kernel<<<nblk(cout * Kpad32), 256, 0, stream>>>(wpart, nwg, Kpad32, cpad, cin, cout, dW);
+    // the operand read at shifted points: the input, or dout where only dout has 8 channels
+    const bool transposed = opad == 8 && cpad == 32;
+    const int cb = transposed ? opad : cpad;
+    const int Kpad32 = round_up(27 * cb, 32);
+    const int64_t planes = (int64_t)batch * n * (n / kWgradTy) * (n / 32);   // planes of 32 x kWgradTy points
+    nwg = (int)std::min<int64_t>(nwg, planes);
+    if (transposed)
+        conv_wgrad_kernel<32, 8, -1><<<nwg, kWgradThreads, 0, stream>>>(in, dout, n, planes, wpart);
+    else if (cpad == 32)
+        conv_wgrad_kernel<32, 32, 1><<<nwg, kWgradThreads, 0, stream>>>(dout, in, n, planes, wpart);
+    else if (opad == 32)
+        conv_wgrad_kernel<32, 8, 1><<<nwg, kWgradThreads, 0, stream>>>(dout, in, n, planes, wpart);
+    else
+        conv_wgrad_kernel<8, 8, 1><<<nwg, kWgradThreads, 0, stream>>>(dout, in, n, planes, wpart);
+    wgrad_reduce_kernel<<<nblk((transposed ? cin : cout) * Kpad32), 256, 0, stream>>>(wpart, nwg, Kpad32, cb, cin, cout,
+                                                                                      transposed, dW);
     if (db) {
         bias_grad_kernel<<<kBiasWg, 256, 0, stream>>>(dout, opad, (int64_t)batch * n * n * n, bpart);
         bias_grad_final_kernel<<<1, 256, 0, stream>>>(bpart, kBiasWg, cout, db);

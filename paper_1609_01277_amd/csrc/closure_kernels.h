@@ -415,150 +415,190 @@ __global__ void __launch_bounds__(256) gelu_bwd_kernel(const float* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient on MFMA:  dW[o][kk] = sum_p dout[p][o] * in[p + off(tap)][c]
-// (o < 32 rows, kk < Kpad32 columns).  A workgroup takes blocks of 32
-// consecutive x-points of one (b, y, z) row (n % 32 == 0).  Per block it stages
-// in LDS, transposed so the reduction over points is contiguous:
-//   sd[o][32]                       dout of the block
-//   si[tap][c][32]                  input shifted by each of the 27 taps
-// then each wave accumulates its share of the Kpad32/32 column tiles.
-// A staging thread loads 8 channels of 10 consecutive points of one (dz, dy)
-// row (ten 16-byte loads: 8 points and one on each side), and for each of the
-// three x-shifts transposes an 8 x 8 block in registers and stores 8 points of
-// one channel per 16-byte LDS store; each input element is loaded once per
-// (dz, dy) instead of once per tap.  LDS rows are padded to 40 elements (80 bytes)
-// so that rows 8 or 32 apart, and the 32 rows one MFMA operand read spans, do
-// not fall on the same banks.
-// Results: per-workgroup partial sums part[wg][32][Kpad32] (FP32).
-constexpr int kWgradMaxTiles = 28;   // Kpad32 / 32 <= 28 (27 * 32 = 864)
-constexpr int kWgradRow = 40;        // LDS row length (elements) of sd and si
+// Weight gradient on MFMA: dW[o][tap][c] = sum_p dout[p][o] * in[p + off(tap)][c]
+//                                        = sum_p dout[p - off(tap)][o] * in[p][c].
+// One of the two tensors is read at p (`a`, CA channels: the M side), the other at
+// p + SIGN off(tap) (`b`, CB channels: the N side, a tile of 32 columns being one tap of
+// 32 channels or four taps of 8).  a = dout, b = in, SIGN = 1, except for 8 output and 32
+// input channels, where a = in, b = dout, SIGN = -1 leaves 7 tiles instead of 27 that are
+// three quarters padding.  K runs over points, so both operands need 8 consecutive points
+// of one channel in a lane, and the tensors are channel-last: ds_read_b64_tr_b16 makes
+// that transpose on the way from LDS (16 lanes give the addresses of 4 rows of 16 values
+// and get 4 points of one channel each), so a plane is staged as it lies in memory, once.
+// The former kernel transposed in registers and wrote every tap's shifted copy to LDS
+// for each block of 32 points: 218 us a call (64^3, batch 4, the three layers' mean), two
+// thirds of it waiting.  This one: 44 us (83 us for 32 and 32 channels, 25 us with 8 on a side).
+// A workgroup marches up a column of 32 x kWgradTy points in z.  LDS holds four planes of
+// b with their halo (z - 1 .. z + 1 and the one being written) and two of a; the next
+// planes are requested before the products of the present one: one barrier a plane.  Its
+// bound is LDS: 4 reads of 4 cycles a product of 32 for one tile, 2.5 for four tiles.
+// Results: per-workgroup partial sums part[wg][32][Kpad32] (FP32), rows the channels of a,
+// columns tap * CB + channel of b.
+constexpr int kWgradTy = 8;
+constexpr int kWgradThreads = 512;
+typedef short sbli_v4s __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) sbli_v4s* sbli_lds_v4s;
 
-// o[j][k] = r[k][j]: the 8 x 8 block of 16-bit elements transposed.
-__device__ __forceinline__ void transpose8x8(const bf16x8 (&r)[8], bf16x8 (&o)[8]) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) o[j][k] = r[k][j];
+// 8 consecutive points (rows `stride` elements apart) of one channel for the MFMA operand
+// of this lane; p is this lane's address of the first 4 rows.
+__device__ __forceinline__ bf16x8 read_points_tr(const __bf16* p, int stride) {
+    const sbli_v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sbli_lds_v4s)(p));
+    const sbli_v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((sbli_lds_v4s)(p + 4 * stride));
+    typedef short v8s __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, (v8s)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__global__ void __launch_bounds__(256) conv_wgrad_kernel(const __bf16* __restrict__ in, int cpad,
-                                                         const __bf16* __restrict__ dout, int opad, int n,
-                                                         int64_t nblocks, int Kpad32, float* __restrict__ part) {
-    __shared__ __attribute__((aligned(16))) __bf16 sd[32][kWgradRow];
-    __shared__ __attribute__((aligned(16))) __bf16 si[27 * 32][kWgradRow];   // [(tap * cpad + c)][point]
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int row = lane & 31, half = lane >> 5;
-    const int ntiles = Kpad32 / 32;
-    const int nrows = n / 32;            // 32-point blocks per x-row
+template <int CA, int CB, int SIGN>
+__global__ void __launch_bounds__(kWgradThreads, 2)
+    conv_wgrad_kernel(const __bf16* __restrict__ a, const __bf16* __restrict__ b, int n, int64_t planes,
+                      float* __restrict__ part) {
+    constexpr int TX = 32, TY = kWgradTy, NT = kWgradThreads, NW = NT / 64;
+    constexpr int HX = TX + 2, HY = TY + 2, HP = HX * HY;
+    constexpr int LA = CA == 32 ? 40 : 8, LB = CB == 32 ? 40 : 8;   // LDS point strides (80 or 16 bytes)
+    constexpr int TILES = CB == 32 ? 27 : 7, TPW = (TILES + NW - 1) / NW;
+    constexpr int KP = TILES * 32;
+    constexpr int NAC = TX * TY * CA / 8, NBC = HP * CB / 8;        // 16-byte pieces of a plane
+    constexpr int ITA = (NAC + NT - 1) / NT, ITB = (NBC + NT - 1) / NT;
+    __shared__ __attribute__((aligned(16))) __bf16 sa[2][TX * TY * LA];
+    __shared__ __attribute__((aligned(16))) __bf16 sb[4][HP * LB];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t P = (int64_t)n * n * n;
-    floatx16 acc[7];
+    const int ctx = n / TX, cty = n / TY;
+    // this lane's address within 16 points: row (of 4) and first channel of its 8-byte piece;
+    // lanes 0-15 / 16-31 serve columns 0-15 / 16-31, lanes 32-63 the upper 8 points
+    const int r4 = (lane & 15) >> 2, c4 = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    const int row0 = (lane >> 5) * 8 + r4;
+    const int laneA = row0 * LA + (CA == 32 ? c4 : c4 & 7);
+    const bool a_valid = CA == 32 || (lane & 31) < 8;               // rows of a beyond its 8 channels are zero
+    int laneB[TPW], dzB[TPW];
 #pragma unroll
-    for (int i = 0; i < 7; ++i)
+    for (int i = 0; i < TPW; ++i) {
+        const int tile = min(wave + NW * i, TILES - 1);
+        const int tap = CB == 32 ? tile : min(4 * tile + c4 / 8, 26);   // the 28th tap's columns are never read back
+        dzB[i] = SIGN * (tap / 9 - 1);
+        laneB[i] = ((1 + SIGN * (tap / 3 % 3 - 1)) * HX + 1 + SIGN * (tap % 3 - 1) + row0) * LB +
+                   (CB == 32 ? c4 : c4 & 7);
+    }
+    floatx16 acc[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i)
+#pragma unroll
         for (int j = 0; j < 16; ++j) acc[i][j] = 0.0f;
-    const int64_t per = (nblocks + gridDim.x - 1) / gridDim.x;
-    const int64_t blk0 = (int64_t)blockIdx.x * per;
-    const int64_t blk1 = blk0 + per < nblocks ? blk0 + per : nblocks;
-    for (int64_t blk = blk0; blk < blk1; ++blk) {
-        // decode block -> (b, z, y, x0)
-        const int xb = (int)(blk % nrows);
-        const int64_t r = blk / nrows;
-        const int y = (int)(r % n);
-        const int z = (int)((r / n) % n);
-        const int64_t b = r / ((int64_t)n * n);
-        const int x0 = xb * 32;
-        __syncthreads();   // previous block's LDS reads are done
-        // stage dout: 32 points x opad channels, 8 points x 8 channels per thread
-        for (int t = threadIdx.x; t < 4 * (opad / 8); t += blockDim.x) {
-            const int pg = t % 4, cg = t / 4;
-            const int64_t g = b * P + ((int64_t)z * n + y) * n + x0 + pg * 8;
-            bf16x8 r[8], o[8];
+    const int64_t per = (planes + gridDim.x - 1) / gridDim.x;
+    const int64_t u1 = min(((int64_t)blockIdx.x + 1) * per, planes);
+    int64_t u = (int64_t)blockIdx.x * per;
+    while (u < u1) {
+        // planes z0 .. z1 - 1 of one column
+        const int64_t colid = u / n;
+        const int z0 = (int)(u % n);
+        const int z1 = (int)min((int64_t)n, z0 + (u1 - u));
+        u += z1 - z0;
+        const int x0 = (int)(colid % ctx) * TX, y0 = (int)(colid / ctx % cty) * TY;
+        const int64_t smp = colid / ctx / cty;
+        const __bf16* as = a + smp * P * CA;
+        const __bf16* bs = b + smp * P * CB;
+        bf16x8 ra[ITA], rb[ITB];
+        auto load_a = [&](int z) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) r[k] = *(const bf16x8*)(dout + (g + k) * opad + cg * 8);
-            transpose8x8(r, o);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) *(bf16x8*)(&sd[cg * 8 + j][pg * 8]) = o[j];
-        }
-        for (int t = threadIdx.x; t < (32 - opad) * 4; t += blockDim.x) {
-            bf16x8 zero;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) zero[j] = (__bf16)0.0f;
-            *(bf16x8*)(&sd[opad + t / 4][(t % 4) * 8]) = zero;
-        }
-        // stage the input for every tap: one (dz, dy) row segment per thread item
-        for (int t = threadIdx.x; t < 9 * 4 * (cpad / 8); t += blockDim.x) {
-            const int pg = t % 4;
-            const int rest = t / 4;
-            const int cg = rest % (cpad / 8);
-            const int zy = rest / (cpad / 8);              // (dz + 1) * 3 + (dy + 1)
-            const int dz = zy / 3 - 1, dy = zy % 3 - 1;
-            const int64_t row = b * P + ((int64_t)wrapn(z + dz, n) * n + wrapn(y + dy, n)) * n;
-            bf16x8 r[10];
-#pragma unroll
-            for (int k = 0; k < 10; ++k)
-                r[k] = *(const bf16x8*)(in + (row + wrapn(x0 + pg * 8 + k - 1, n)) * cpad + cg * 8);
-#pragma unroll
-            for (int sx = 0; sx < 3; ++sx) {                // dx = sx - 1
-                const int tap = zy * 3 + sx;
-                bf16x8 blk[8], o[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) blk[k] = r[k + sx];
-                transpose8x8(blk, o);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) *(bf16x8*)(&si[tap * cpad + cg * 8 + j][pg * 8]) = o[j];
+            for (int k = 0; k < ITA; ++k) {
+                const int e = min(tid + NT * k, NAC - 1), pt = e / (CA / 8), g = e % (CA / 8);
+                ra[k] = *(const bf16x8*)(as + (((int64_t)z * n + y0 + pt / TX) * n + x0 + pt % TX) * CA + g * 8);
             }
-        }
-        __syncthreads();
-        // A[o][pts] from sd, B[pts][kk] from si; two k-steps of 16 points
+        };
+        auto load_b = [&](int z) {
+            const int64_t gz = (int64_t)wrapn(z, n) * n;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const bf16x8 av = *(const bf16x8*)(&sd[row][ks * 16 + half * 8]);
+            for (int k = 0; k < ITB; ++k) {
+                const int e = min(tid + NT * k, NBC - 1), pt = e / (CB / 8), g = e % (CB / 8);
+                const int gy = wrapn(y0 + pt / HX - 1, n), gx = wrapn(x0 + pt % HX - 1, n);
+                rb[k] = *(const bf16x8*)(bs + ((gz + gy) * n + gx) * CB + g * 8);
+            }
+        };
+        auto store_a = [&](int buf) {
 #pragma unroll
-            for (int i = 0; i < 7; ++i) {
-                const int tile = wave + 4 * i;
-                if (tile < ntiles) {
-                    const int kk = tile * 32 + row;
-                    bf16x8 bv;
-                    if (kk < 27 * cpad) {
-                        bv = *(const bf16x8*)(&si[kk][ks * 16 + half * 8]);
-                    } else {
+            for (int k = 0; k < ITA; ++k) {
+                const int e = tid + NT * k;
+                if (e < NAC) *(bf16x8*)(&sa[buf][e / (CA / 8) * LA + e % (CA / 8) * 8]) = ra[k];
+            }
+        };
+        auto store_b = [&](int buf) {
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) bv[j] = (__bf16)0.0f;
+            for (int k = 0; k < ITB; ++k) {
+                const int e = tid + NT * k;
+                if (e < NBC) *(bf16x8*)(&sb[buf][e / (CB / 8) * LB + e % (CB / 8) * 8]) = rb[k];
+            }
+        };
+        __syncthreads();   // the previous column's products are done
+        load_b(z0 - 1);
+        store_b((z0 + 3) & 3);
+        load_b(z0);
+        store_b(z0 & 3);
+        load_b(z0 + 1);
+        load_a(z0);
+        for (int z = z0; z < z1; ++z) {
+            store_b((z + 1) & 3);
+            store_a(z & 1);
+            __syncthreads();
+            if (z + 1 < z1) {
+                load_b(z + 2);
+                load_a(z + 1);
+            }
+            const __bf16* pa = &sa[z & 1][laneA];
+            const __bf16* pb[TPW];
+#pragma unroll
+            for (int i = 0; i < TPW; ++i) pb[i] = &sb[(z + dzB[i]) & 3][laneB[i]];
+#pragma unroll
+            for (int y = 0; y < TY; ++y)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    bf16x8 av = read_points_tr(pa + (y * TX + ks * 16) * LA, LA);
+                    if (CA == 8) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) av[j] = a_valid ? av[j] : (__bf16)0.0f;
                     }
-                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[i], 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < TPW; ++i) {
+                        if (wave + NW * i < TILES) {   // the same for a whole wavefront
+                            const bf16x8 bv = read_points_tr(pb[i] + (y * HX + ks * 16) * LB, LB);
+                            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[i], 0, 0, 0);
+                        }
+                    }
                 }
-            }
         }
     }
-    // D[o][kk]: kk = tile*32 + (lane & 31), o = (j/4)*8 + half*4 + (j&3)
-    float* dst = part + (int64_t)blockIdx.x * 32 * Kpad32;
+    // D[m][kk]: kk = tile * 32 + (lane & 31), m = (j / 4) * 8 + (lane >> 5) * 4 + (j & 3)
+    float* dst = part + (int64_t)blockIdx.x * 32 * KP;
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        const int tile = wave + 4 * i;
-        if (tile >= ntiles) continue;
+    for (int i = 0; i < TPW; ++i) {
+        const int tile = wave + NW * i;
+        if (tile >= TILES) continue;
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int o = (j / 4) * 8 + half * 4 + (j & 3);
-            dst[(int64_t)o * Kpad32 + tile * 32 + row] = acc[i][j];
+            const int m = (j / 4) * 8 + (lane >> 5) * 4 + (j & 3);
+            dst[(int64_t)m * KP + tile * 32 + (lane & 31)] = acc[i][j];
         }
     }
 }
 
 // Sums the per-workgroup partials in a fixed order and writes the gradient of
-// a layer in the master layout dW[o][c][tap] (o < cout, c < cin).
+// a layer in the master layout dW[o][c][tap] (o < cout, c < cin).  Rows of a partial
+// are output channels and its columns tap * cb + input channel, or (transposed) rows
+// input channels and columns tap * cb + output channel.
 __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float* __restrict__ part, int nwg, int Kpad32,
-                                                           int cpad, int cin, int cout, float* __restrict__ dW) {
-    // one thread per (o, kk), kk = tap * cpad + c fastest, so the partial rows
+                                                           int cb, int cin, int cout, int transposed,
+                                                           float* __restrict__ dW) {
+    // one thread per (row, kk), kk fastest, so the partial rows
     // are read contiguously.  Four interleaved accumulators (partials w = 4i + j
     // into s_j) keep four loads in flight; they are combined in a fixed order,
     // so the result is deterministic.
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
     const int kk = id % Kpad32;
-    const int o = id / Kpad32;
-    if (o >= cout) return;
-    const int tap = kk / cpad, c = kk % cpad;
-    if (tap >= 27 || c >= cin) return;
-    const float* p = part + (int64_t)o * Kpad32 + kk;
+    const int row = id / Kpad32;
+    const int tap = kk / cb, ch = kk % cb;
+    const int o = transposed ? ch : row, c = transposed ? row : ch;
+    if (tap >= 27 || o >= cout || c >= cin) return;
+    const float* p = part + (int64_t)row * Kpad32 + kk;
     const int64_t stride = (int64_t)32 * Kpad32;
     float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
     int w = 0;
