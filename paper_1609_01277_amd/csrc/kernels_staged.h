@@ -44,9 +44,8 @@ namespace sbli {
 // axis, which keeps a workgroup's LDS small enough that registers, not LDS, bound the
 // number of workgroups per CU up to order 12.
 constexpr int kStagedTile = 16;
-// Planes per run of the z-marching nested-field step (2R planes of the own
-// column are loaded ahead of each run).  Runs of 32 and 128 measure the same at
-// 512^3, orders 8 and 12.
+// Planes per run of the z-marching nested-field step where its tiles fill the chip (see
+// nested_run).  Runs of 32 and 128 measure the same at 512^3, orders 8 and 12.
 constexpr int kNestedRun = 64;
 // Fields of a strip: rho, rho E, Th, u_i, then W_d, G_d of the strip's axis d (see
 // nested_terms), then the momentum where LDS keeps it (kMomentumInLds).

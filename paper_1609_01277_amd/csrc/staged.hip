@@ -3,7 +3,37 @@
 #include "kernels_staged.h"
 #include "staged.h"
 
+#include <algorithm>
+
 namespace sbli {
+
+// Planes per run of the nested-field step.  A workgroup (a tile and a run) fills a CU, and
+// the plane loop is one chain, so few long runs leave the chip idle (96^3 in 32x32 tiles
+// and runs of 64 planes: 18 workgroups) and a number of them just over a multiple of the
+// CUs costs a further round; each run loads 2R planes of its own columns first, worth
+// about R planes of the loop.  So: the run that makes rounds x (planes + R) least, up to
+// 160 planes (runs of 32, 64 and 128 measure the same at 512^3).  Both steps, us a stage,
+// runs of 64 -> this: 32^3, FP64, order 8: 100 -> 22; 64^3: 222 -> 36; 96^3: 268 -> 92;
+// 128^3: 379 -> 198; 160^3: 514 -> 377; 256^3 keeps 64 (1,490; 32: 1,507; 128: 1,681).
+static int nested_run(int tiles, int nz, int R) {
+    const int cus = 256;
+    int best = std::min(nz, kNestedRun);
+    auto cost = [&](int zc) {
+        const int64_t units = (int64_t)tiles * ((nz + zc - 1) / zc);
+        return ((units + cus - 1) / cus) * (zc + R);
+    };
+    int64_t least = cost(best);
+    for (int rounds = 1; rounds <= 4; ++rounds) {
+        const int runs = std::min(rounds * cus / tiles, nz);
+        if (runs < 1) continue;
+        const int zc = (nz + runs - 1) / runs;
+        if (zc <= 160 && cost(zc) < least) {
+            best = zc;
+            least = cost(zc);
+        }
+    }
+    return best;
+}
 
 template <typename T, int R>
 static void staged_run(const StagedArgs& a, const T* qin, T* dq, T* qout, T* nf) {
@@ -18,7 +48,7 @@ static void staged_run(const StagedArgs& a, const T* qin, T* dq, T* qout, T* nf)
         // x-arms, 32-byte row pieces of 128-byte lines, for four times as many own points.
         constexpr int TN = (sizeof(T) == 8 && R > 4) ? kStagedTile : 2 * kStagedTile;
         const int tx = (c.n[0] + TN - 1) / TN, ty = (c.n[1] + TN - 1) / TN;
-        const int zn = kNestedRun;
+        const int zn = nested_run(tx * ty, c.n[2], R);
         if (sizeof(T) == 4 && a.mode == kModeRHS)   // kPlain
             staged_nested_zring_kernel<T, R, TN, kPlain<T, kModeRHS>><<<grid_of(tx * ty, zn), TN * TN, 0, a.stream>>>(
                 qin, nf, c, tx, ty, zn);
