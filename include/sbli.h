@@ -146,22 +146,25 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  * workgroup ("zchunk") they fix the launch configuration.  The last variant of
  * every (dtype, order) is the staged form: two launches, one thread per point,
  * with the nested fields (6 words per point) in library-owned device memory,
- * allocated when the form is first selected and kept until sbli_destroy; orders 10 and 12 have only this variant, selected at
- * sbli_init.  All variants compute bitwise identical results; only speed differs.
+ * allocated when the form is first selected and kept until sbli_destroy; orders 10 and 12
+ * have only this variant.  All variants compute bitwise identical results; only speed
+ * differs.  sbli_init selects a variant and a zchunk by the grid's size: the staged form
+ * for orders 6 (FP32: up to 96^3 points) and 8 while its scratch is at most 1/64 of the
+ * device's free memory, else a fused variant and a zchunk that fill the device.
  *
  * sbli_num_variants: number of variants for the context (>= 1), or < 0 on error.
  * sbli_variant_info: info = {tile x, tile y, load-ahead depth, register-window
  *   rotation (1) or shifting (0), wavefronts per SIMD its register allocation
  *   allows at least (1: as many registers as the kernel wants), barrier
  *   schedule (0: two barriers per z-plane; 1: double-buffered LDS planes, one
- *   barrier, where the R planes below the output plane are kept (0: registers,
+ *   barrier; 2: one barrier, the work split between two kinds of wavefronts), where the R planes below the output plane are kept (0: registers,
  *   1: LDS)} of a variant (7 ints written); all seven are 0 for the staged form.
  * sbli_set_tuning / sbli_get_tuning: select / read the variant and zchunk used
  *   by sbli_rhs and sbli_rk3_step (1 <= zchunk <= nz; the staged form ignores
  *   zchunk).  sbli_set_tuning waits for the context's stream (it updates a small
  *   device table).  Selecting the staged form may allocate its scratch
  *   (SBLI_ERR_ALLOC if that fails; the previous selection then stays).
- * sbli_autotune: time every variant with several zchunks (hipEvents on the
+ * sbli_autotune: time every variant with several zchunks, the one sbli_init's rule would give it among them (hipEvents on the
  *   context's stream, `reps` RK3 steps each after one warm-up step) using the
  *   caller's device buffers, then select the fastest (a later candidate replaces
  *   the best so far only when more than 1 % faster, so near-ties resolve to the

@@ -103,16 +103,6 @@ static void fill_const(const sbli_ctx* x, BoxConst<T>& c) {
     for (int d = 0; d < 3; ++d) c.sym[d] = x->p.bc[d] == SBLI_BC_SYMMETRY;
 }
 
-// z-planes per workgroup: long enough to amortise the 4R-plane pipeline fill,
-// short enough to give the 256 compute units several workgroups each.
-static int default_zchunk(const sbli_ctx* x) {
-    const int tx = 16, ty = 16;
-    const long tiles = (long)((x->p.nx + tx - 1) / tx) * ((x->p.ny + ty - 1) / ty);
-    int zc = x->p.nz;
-    while (zc > 32 && tiles * ((x->p.nz + zc - 1) / zc) < 2048) zc = (zc + 1) / 2;
-    return zc;
-}
-
 // Variants of a context: the compiled fused variants of (dtype, order) (none
 // beyond order 8), then the staged form (all fields of the StageVariant 0).
 static int num_fused(const sbli_ctx* ctx) {
@@ -136,6 +126,101 @@ static int64_t npoints(const sbli_ctx* x);
 static hipError_t ensure_staged_scratch(sbli_ctx* x) {
     if (x->stg) return hipSuccess;
     return hipMalloc(&x->stg, (size_t)kStagedScratchWords * (size_t)npoints(x) * elem_size(x));
+}
+
+// Default launch configuration.  A workgroup of the fused kernel takes zchunk + 4R serial
+// steps of one plane, and the chip runs 256 workgroups at a time; its time is modelled as
+// (zchunk + 4R) plane_us (1 + beside (rounds - 1)), rounds = ceil(workgroups / 256): a
+// small grid takes chunks of a few planes (32^3: of one), a large one the longest that
+// still fill the last round.  Each (type, radius) has one or two variants to choose from,
+// a small tile for small grids and the one that is fastest on large grids; `beside` < 1
+// where two workgroups fit a CU.  Within 15 % of the fastest of all variants and chunks
+// from 20^3 to 256^3.  Measured us a stage, first variant with chunks of 32
+// planes or the whole grid -> this choice (and the fastest of all variants and chunks),
+// FP64 order 4: 32^3 71 -> 12 (12), 64^3 76 -> 24 (24), 96^3 66 -> 47 (47), 160^3 237 ->
+// 179 (179), 256^3 742 -> 592 (592); FP32 order 4: 75 -> 11 (11), 78 -> 18 (18), 69 -> 34
+// (34), 127 -> 98 (98), 392 -> 335 (335).
+struct LaunchCand {
+    int variant;        // index into the variant list of (type, radius)
+    double plane_us;    // a workgroup's time for a plane with a CU to itself
+    double beside;      // cost of a further round relative to the first
+};
+
+static const LaunchCand* launch_cands(int dtype, int r, int& n) {
+    static const LaunchCand d1[] = {{3, 1.2, 0.8}, {2, 1.6, 0.8}}, d2[] = {{1, 1.35, 0.75}, {0, 1.7, 1.0}},
+                            d3[] = {{1, 2.0, 1.0}}, d4[] = {{4, 2.4, 1.0}}, f1[] = {{3, 0.9, 0.8}, {2, 1.2, 0.8}},
+                            f2[] = {{4, 1.4, 1.0}, {0, 1.95, 1.0}}, f3[] = {{3, 1.5, 1.0}}, f4[] = {{2, 1.9, 0.35}};
+    const bool d = dtype == SBLI_F64;
+    n = r <= 2 ? 2 : 1;
+    switch (r) {
+        case 1: return d ? d1 : f1;
+        case 2: return d ? d2 : f2;
+        case 3: return d ? d3 : f3;
+        default: return d ? d4 : f4;
+    }
+}
+
+static StageVariant fused_variant(int dtype, int r, int v) {
+    return dtype == SBLI_F64 ? StageDispatch<double>::get(r, v) : StageDispatch<float>::get(r, v);
+}
+
+constexpr int kCus = 256;
+
+// The chunk that makes the modelled time of variant v over `count` boxes least; *cost
+// receives it (in plane times).
+static int best_zchunk(int dtype, int r, int v, double beside, const sbli_params* p, int count, double* cost) {
+    const StageVariant sv = fused_variant(dtype, r, v);
+    int zmax = 1, best = 1;
+    for (int i = 0; i < count; ++i) zmax = std::max(zmax, p[i].nz);
+    *cost = HUGE_VAL;
+    for (int zc = 1; zc <= zmax; ++zc) {
+        double units = 0;
+        for (int i = 0; i < count; ++i)
+            units += (double)((p[i].nx + sv.tx - 1) / sv.tx) * ((p[i].ny + sv.ty - 1) / sv.ty) *
+                     ((p[i].nz + zc - 1) / zc);
+        const double rounds = std::max(1.0, std::ceil(units / kCus));
+        const double t = (zc + 4 * r) * (1.0 + beside * (rounds - 1.0));
+        if (t < *cost) {
+            *cost = t;
+            best = zc;
+        }
+    }
+    return best;
+}
+
+static void choose_fused(int dtype, int r, const sbli_params* p, int count, int* variant, int* zchunk) {
+    int n = 0;
+    const LaunchCand* c = launch_cands(dtype, r, n);
+    double least = HUGE_VAL;
+    for (int k = 0; k < n; ++k) {
+        double t = 0;
+        const int zc = best_zchunk(dtype, r, c[k].variant, c[k].beside, p, count, &t);
+        if (t * c[k].plane_us < least) {
+            least = t * c[k].plane_us;
+            *variant = c[k].variant;
+            *zchunk = zc;
+        }
+    }
+}
+
+// Where the staged form is the default.  Order 8, and order 6 in FP64: it is the faster
+// one on every grid (us a stage, fused in its best configuration against staged: FP64
+// order 6, 32^3: 25, 20; 64^3: 64, 32; 128^3: 377, 184; 256^3: 2,998, 1,369; FP32 order 8:
+// 27, 16; 50, 26; 221, 123; 1,629, 976).  FP32 order 6: up to about 96^3 (17, 15; 27, 24;
+// 96^3: 55, 55; 128^3: 93, 116; 256^3: 637, 911).  Not at orders 2 and 4 (FP64 order 4:
+// 12, 17; 24, 28; 91, 164; 654, 1,236).  Its scratch is allocated with the context, so a
+// grid only defaults to it while that is a small part of the free memory: a program that
+// fills the device with states is not made to run out of it.
+static bool prefers_staged(const sbli_params* p, int r) {
+    const int64_t P = (int64_t)p->nx * p->ny * p->nz;
+    if (r < 3 || (r == 3 && p->dtype == SBLI_F32 && P > 96 * 96 * 96)) return false;
+    size_t free_b = 0, total = 0;
+    if (hipMemGetInfo(&free_b, &total) != hipSuccess) {
+        (void)hipGetLastError();   // the fused form needs no scratch
+        return false;
+    }
+    const double scratch = (double)kStagedScratchWords * P * (p->dtype == SBLI_F64 ? 8 : 4);
+    return scratch <= free_b / 64.0;
 }
 
 // Rebuilds the box's launch-table entry for the current variant and zchunk and
@@ -176,7 +261,8 @@ static bool overlaps(const void* a, const void* b, size_t bytes) {
     return pa < pb + bytes && pb < pa + bytes;
 }
 
-extern "C" int sbli_init(const sbli_params* p, void* hip_stream, sbli_ctx** out) {
+// sbli_init; a box of a batch keeps to the fused form.
+static int init_ctx(const sbli_params* p, void* hip_stream, bool in_batch, sbli_ctx** out) {
     if (!out) return fail(nullptr, SBLI_ERR_ARG, "sbli_init: out is NULL");
     *out = nullptr;
     if (!p) return fail(nullptr, SBLI_ERR_ARG, "sbli_init: params is NULL");
@@ -213,13 +299,21 @@ extern "C" int sbli_init(const sbli_params* p, void* hip_stream, sbli_ctx** out)
     fill_const(x, x->c64);
     fill_const(x, x->c32);
 
-    x->zchunk = default_zchunk(x);
+    x->zchunk = p->nz;
     x->variant = 0;
     hipError_t e = hipGetDevice(&x->device);
     if (e == hipSuccess) e = hipMalloc((void**)&x->diag_part, sizeof(double) * kDiagBlocks * (2 * kDiagQ + 3));
     if (e == hipSuccess) e = hipMalloc((void**)&x->diag_da, sizeof(double) * 3 * kMaxR);
     if (e == hipSuccess) e = hipMalloc((void**)&x->diag_out, sizeof(double) * 10);
     if (e == hipSuccess) e = hipMalloc(&x->inst_dev, sizeof(BoxInst<double>));
+    if (e == hipSuccess && num_fused(x) > 0) {
+        if (!in_batch && prefers_staged(p, x->r) && ensure_staged_scratch(x) == hipSuccess) {
+            x->variant = num_fused(x);
+        } else {
+            (void)hipGetLastError();   // of the scratch: the fused form runs without it
+            choose_fused(p->dtype, x->r, p, 1, &x->variant, &x->zchunk);
+        }
+    }
     if (e == hipSuccess) e = update_table(x);
     if (e == hipSuccess) {
         double da[3 * kMaxR];
@@ -242,6 +336,10 @@ extern "C" int sbli_init(const sbli_params* p, void* hip_stream, sbli_ctx** out)
     }
     *out = x;
     return SBLI_OK;
+}
+
+extern "C" int sbli_init(const sbli_params* p, void* hip_stream, sbli_ctx** out) {
+    return init_ctx(p, hip_stream, false, out);
 }
 
 extern "C" int sbli_destroy(sbli_ctx* ctx) {
@@ -466,7 +564,13 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
     int bv = ctx->variant, bz = ctx->zchunk;
     for (int v = 0; v < num_variants(ctx); ++v) {
         // the staged form has no z-chunks; it is skipped when its scratch cannot be allocated
-        for (int ci = 0; ci < (is_staged(ctx, v) ? 1 : nc); ++ci) {
+        int nv = is_staged(ctx, v) ? 1 : nc;
+        if (!is_staged(ctx, v)) {   // and the chunk that the launch model prefers
+            double t;
+            const int zc = best_zchunk(ctx->p.dtype, ctx->r, v, 1.0, &ctx->p, 1, &t);
+            if (std::find(cands, cands + nc, zc) == cands + nc) cands[nv++] = zc;
+        }
+        for (int ci = 0; ci < nv; ++ci) {
             ctx->variant = v;
             ctx->zchunk = cands[ci];
             if (update_table(ctx) != hipSuccess) {
@@ -682,17 +786,19 @@ extern "C" int sbli_batch_init(const sbli_instance* inst, int count, int order, 
     b->stream = (hipStream_t)hip_stream;
     b->inst.assign(inst, inst + count);
     b->off.assign(count + 1, 0);
+    std::vector<sbli_params> box_params;
     for (int i = 0; i < count; ++i) {
         sbli_params p{inst[i].n, inst[i].n, inst[i].n, 2 * M_PI, 2 * M_PI, 2 * M_PI, inst[i].Re, inst[i].Mach,
                       inst[i].Pr, inst[i].gamma, order, dtype};
         sbli_ctx* c = nullptr;
-        int rc = sbli_init(&p, hip_stream, &c);
+        int rc = init_ctx(&p, hip_stream, true, &c);
         if (rc != SBLI_OK) {
             bfail(nullptr, rc, "sbli_batch_init: instance %d: %s", i, sbli_last_error(nullptr));
             sbli_batch_destroy(b);
             return rc;
         }
         b->ctx.push_back(c);
+        box_params.push_back(p);
         b->off[i + 1] = b->off[i] + 5 * (size_t)inst[i].n * inst[i].n * inst[i].n;
     }
     hipError_t e = hipMalloc(&b->table_dev, sizeof(BoxInst<double>) * count);
@@ -702,6 +808,7 @@ extern "C" int sbli_batch_init(const sbli_instance* inst, int count, int order, 
         sbli_batch_destroy(b);
         return SBLI_ERR_HIP;
     }
+    choose_fused(dtype, b->r, box_params.data(), count, &b->variant, &b->zmax);
     int rc = batch_build_table(b);
     if (rc != SBLI_OK) {
         g_batch_err = b->err;
