@@ -191,6 +191,16 @@ __device__ __forceinline__ PF<T> centre_xy(PF<T> s) {
     return s;
 }
 
+// FP64 at orders 6 and up: the z sums form the momentum likewise, rho u at the point and
+// its neighbours, so that a register window of 2R + 1 planes need not hold it.
+template <typename T, int R>
+constexpr bool kMomentumFromU = !kMomentumInLds<T> && R >= 3;
+template <typename T, int R>
+__device__ __forceinline__ PF<T> z_point(PF<T> s) {
+    if constexpr (kMomentumFromU<T, R>) return centre_xy(s);
+    return s;
+}
+
 // The nested terms of axis j act on V_j = Re u_i tau_ij and t_j = 2 (g_jj - theta) / (3 Re)
 // (g_ij = D_j u_i, theta = g_kk).  With the point's pressure they become the two
 // fields whose first derivatives enter the residual:
@@ -710,6 +720,7 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
             T dn[5], qn[5];
             if (do_out && interior) {
                 const PF<T>& s = Qb[slot(R)];
+                const PF<T> sz = z_point<T, R>(s);
                 auto below = [&](int m) -> PF<T> {         // point fields of plane o - m
                     if constexpr (ZL) {
                         const int k = (it - m) % R;
@@ -735,12 +746,14 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
     #pragma unroll
                 for (int m = 1; m <= R; ++m) {
                     pair_fence();
-                    rs.template add<2>(s, with_pressure<PL>(Qb[slot(R + m)], c), s_az[(it + m - R) % (2 * R + 1)][0][cy][cx],
-                                       s_az[(it + m - R) % (2 * R + 1)][1][cy][cx], with_pressure<PL>(below(m), c),
+                    rs.template add<2>(sz, z_point<T, R>(with_pressure<PL>(Qb[slot(R + m)], c)),
+                                       s_az[(it + m - R) % (2 * R + 1)][0][cy][cx],
+                                       s_az[(it + m - R) % (2 * R + 1)][1][cy][cx],
+                                       z_point<T, R>(with_pressure<PL>(below(m), c)),
                                        s_az[(it - m - R) % (2 * R + 1)][0][cy][cx],
                                        s_az[(it - m - R) % (2 * R + 1)][1][cy][cx], c, m - 1);
                 }
-                rs.template end<2>(s, c);
+                rs.template end<2>(sz, c);
                 T Rv[5];
                 rs.result(Rv);
                 if (clos != nullptr && __builtin_amdgcn_readfirstlane(cflag[0]) != 0) {   // a uniform branch

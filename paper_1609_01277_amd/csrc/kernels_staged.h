@@ -11,7 +11,8 @@
 //   1. staged_nested_zring_kernel: nf = (V_0, V_1, V_2, t_0, t_1, t_2), the
 //      velocity parts of the nested terms (nested_terms; paper Sec. "Expanding":
 //      the inner derivative of a nested term is taken first);
-//   2. staged_tiled_kernel:  the residual (paper eqs. of mass, momentum and
+//   2. staged_tiled_kernel (one plane of a tile per workgroup) or staged_march_kernel
+//      (kernels_staged_march.h; runs of planes):  the residual (paper eqs. of mass, momentum and
 //      energy in the skew-symmetric form) from q and nf at the 2R neighbours
 //      along each axis, then the 2N Runge-Kutta update.
 //
@@ -45,7 +46,7 @@ namespace sbli {
 // number of workgroups per CU up to order 12.
 constexpr int kStagedTile = 16;
 // Planes per run of the z-marching nested-field step where its tiles fill the chip (see
-// nested_run).  Runs of 32 and 128 measure the same at 512^3, orders 8 and 12.
+// run_planes).  Runs of 32 and 128 measure the same at 512^3, orders 8 and 12.
 constexpr int kNestedRun = 64;
 // Fields of a strip: rho, rho E, Th, u_i, then W_d, G_d of the strip's axis d (see
 // nested_terms), then the momentum where LDS keeps it (kMomentumInLds).
@@ -198,6 +199,7 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             rs.template end<1>(sxy, c);
         }
         {
+            const PF<T> sz = z_point<T, R>(s);
             rs.begin();
 #pragma unroll 1
             for (int m = 1; m <= R; ++m) {
@@ -210,10 +212,11 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
                 b.m2 = flip_sign(b.m2, fb);
                 b.u2 = flip_sign(b.u2, fb);
                 // (a's and b's velocity and V change sign together, and so does W)
-                rs.template add<2>(s, a, W_of(flip_sign(nf[2 * P + ia], fa), a, a.u2), G_of(nf[5 * P + ia], a), b,
+                rs.template add<2>(sz, z_point<T, R>(a), W_of(flip_sign(nf[2 * P + ia], fa), a, a.u2),
+                                   G_of(nf[5 * P + ia], a), z_point<T, R>(b),
                                    W_of(flip_sign(nf[2 * P + ib], fb), b, b.u2), G_of(nf[5 * P + ib], b), c, m - 1);
             }
-            rs.template end<2>(s, c);
+            rs.template end<2>(sz, c);
         }
         if (store) {
             // dq and the new state are streamed (nothing in this launch reads them
