@@ -197,7 +197,7 @@ static int pack_all(sbli_net* net) {
         const Layer& L = net->L[l];
         const int tot = 32 * (L.Kf > L.Kb ? L.Kf : L.Kb);
         pack_weights_kernel<<<nblk(tot), 256, 0, net->stream>>>(net->params + L.w_off, L.cin, L.cout, L.cpad, L.opad,
-                                                                L.Kf, L.Kb, L.Wf, L.Wb);
+                                                                L.Kf, L.Kb, 1, L.Wf, L.Wb);
     }
     NHIP_TRY(net, hipGetLastError());
     return SBLI_OK;
@@ -261,24 +261,25 @@ extern "C" int sbli_net_get_stats(sbli_net* net, float* host_stats) {
 
 // One convolution (implicit GEMM on MFMA, input staged in LDS): `in` has cpad
 // channels per point (8 or 32), epilogue EPI (see closure_kernels.h).  The
-// network and the per-kernel exports launch it through here.
-template <int EPI>
+// network (FRAG: its weights are packed in operand order) and the per-kernel exports
+// (rows, the layout they document) launch it through here.
+template <int EPI, bool FRAG>
 static void conv_launch(hipStream_t stream, int n, const __bf16* in, int cpad, const __bf16* W, int Kpad,
                         const float* bias, int batch, float* fout, __bf16* bout, const float* pre_in, int ocount,
                         int ostride) {
     const unsigned g = (unsigned)((int64_t)batch * n * (n / kConvTy) * (n / kConvTx));
     if (cpad == 32)
-        conv_mfma_lds_kernel<EPI, 32><<<g, 256, 0, stream>>>(in, W, Kpad, bias, n, fout, bout, pre_in, ocount,
+        conv_mfma_lds_kernel<EPI, 32, FRAG><<<g, 256, 0, stream>>>(in, W, Kpad, bias, n, fout, bout, pre_in, ocount,
                                                               ostride);
     else
-        conv_mfma_lds_kernel<EPI, 8><<<g, 256, 0, stream>>>(in, W, Kpad, bias, n, fout, bout, pre_in, ocount,
+        conv_mfma_lds_kernel<EPI, 8, FRAG><<<g, 256, 0, stream>>>(in, W, Kpad, bias, n, fout, bout, pre_in, ocount,
                                                              ostride);
 }
 
 template <int EPI>
 static void conv(sbli_net* net, const __bf16* in, int cpad, const __bf16* W, int Kpad, const float* bias, int batch,
                  float* fout, __bf16* bout, const float* pre_in, int ocount, int ostride) {
-    conv_launch<EPI>(net->stream, net->n, in, cpad, W, Kpad, bias, batch, fout, bout, pre_in, ocount, ostride);
+    conv_launch<EPI, true>(net->stream, net->n, in, cpad, W, Kpad, bias, batch, fout, bout, pre_in, ocount, ostride);
 }
 
 // Weight and bias gradients of one layer: per-workgroup partials, then fixed-order
@@ -490,7 +491,7 @@ extern "C" int sbli_conv3d_pack(const float* W, int cin, int cout, void* Wf, voi
     if (cpad < 0 || opad < 0) return nfail(nullptr, SBLI_ERR_ARG, "sbli_conv3d_pack: cin, cout must be in [1, 32]");
     const int Kf = round_up(27 * cpad, 16), Kb = round_up(27 * opad, 16);
     pack_weights_kernel<<<nblk(32 * (Kf > Kb ? Kf : Kb)), 256, 0, (hipStream_t)hip_stream>>>(
-        W, cin, cout, cpad, opad, Kf, Kb, (__bf16*)Wf, (__bf16*)Wb);
+        W, cin, cout, cpad, opad, Kf, Kb, 0, (__bf16*)Wf, (__bf16*)Wb);
     return launch_status("sbli_conv3d_pack");
 }
 
@@ -506,10 +507,10 @@ extern "C" int sbli_conv3d_fwd(const void* x, int cin, const void* Wf, const flo
     hipStream_t s = (hipStream_t)hip_stream;
     if (act == SBLI_ACT_GELU) {
         if (cout != 32 || !h) return nfail(nullptr, SBLI_ERR_ARG, "%s: GELU layers need cout = 32 and h", fn);
-        conv_launch<kEpiGelu>(s, n, (const __bf16*)x, cpad, (const __bf16*)Wf, Kf, b, batch, pre, (__bf16*)h,
+        conv_launch<kEpiGelu, false>(s, n, (const __bf16*)x, cpad, (const __bf16*)Wf, Kf, b, batch, pre, (__bf16*)h,
                               nullptr, 32, 32);
     } else if (act == SBLI_ACT_NONE) {
-        conv_launch<kEpiLinear>(s, n, (const __bf16*)x, cpad, (const __bf16*)Wf, Kf, b, batch, pre, nullptr,
+        conv_launch<kEpiLinear, false>(s, n, (const __bf16*)x, cpad, (const __bf16*)Wf, Kf, b, batch, pre, nullptr,
                                 nullptr, cout, opad);
     } else {
         return nfail(nullptr, SBLI_ERR_ARG, "%s: act must be SBLI_ACT_NONE or SBLI_ACT_GELU", fn);
@@ -528,10 +529,10 @@ extern "C" int sbli_conv3d_bwd_data(const void* dy, int cout, const void* Wb, in
     const int Kb = round_up(27 * opad, 16);
     hipStream_t s = (hipStream_t)hip_stream;
     if (pre)
-        conv_launch<kEpiDGelu>(s, n, (const __bf16*)dy, opad, (const __bf16*)Wb, Kb, nullptr, batch, nullptr,
+        conv_launch<kEpiDGelu, false>(s, n, (const __bf16*)dy, opad, (const __bf16*)Wb, Kb, nullptr, batch, nullptr,
                                (__bf16*)dx, pre, 32, 32);
     else
-        conv_launch<kEpiData>(s, n, (const __bf16*)dy, opad, (const __bf16*)Wb, Kb, nullptr, batch, (float*)dx,
+        conv_launch<kEpiData, false>(s, n, (const __bf16*)dy, opad, (const __bf16*)Wb, Kb, nullptr, batch, (float*)dx,
                               nullptr, nullptr, 32, 32);
     return launch_status(fn);
 }

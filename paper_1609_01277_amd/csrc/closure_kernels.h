@@ -266,7 +266,8 @@ __global__ void __launch_bounds__(256) box_mean_subtract_kernel(float* __restric
 // A wave computes 2 tiles of 32 points x 32 output channels.  A operand
 // (points x 16 kk): each lane reads 8 consecutive channels of one tap at one
 // point (16 bytes); B operand (16 kk x 32 outputs): 8 consecutive kk of one
-// output channel (16 bytes) from the packed weights Wp[32][Kpad].
+// output channel (16 bytes) from the packed weights Wp[32][Kpad] or, FRAG, from weights
+// packed in operand order.
 // Epilogues:
 //   kEpiGelu   : v = acc + bias; pre[..][o] = v (FP32, 32 ch); act[..][o] = bf16(gelu v)
 //   kEpiLinear : v = acc + bias; y[..][o] = v (FP32, ostride ch) for o < ocount
@@ -279,19 +280,30 @@ enum { kEpiGelu = 0, kEpiLinear = 1, kEpiDGelu = 2, kEpiData = 3 };
 // rows 2w and 2w + 1 as its two 32-point M tiles).  The
 // 34 x 10 x 3 input points it reads (periodic halo of one point) are loaded
 // once into LDS and every one of the 27 taps reads its A operands from there,
-// instead of from global memory 27 times.  LDS point stride: cpad + 8 channels
-// for cpad = 32 (80 bytes: eight lanes' 16-byte reads fall in distinct banks),
-// cpad for cpad = 8.
+// instead of from global memory 27 times.  LDS point stride: cpad channels; for
+// cpad = 32 (64 bytes) the four 16-byte groups of a point are rotated by its x (group ^
+// (hx / 2) % 4), so that eight lanes' reads fall in distinct banks, and two workgroups fit
+// a CU (65 KB; with 80-byte points one did).
+// What bounds it: with weights by rows (Wp[32][Kpad]) a step's load touched 32 lines, and
+// L1 was busy 78 % of the time, MFMA 17 %; in operand order it is one contiguous KB.  Then
+// the chain of a step: its weights' and points' latency, hidden by requests 6 steps and 1
+// step ahead.  4 x 64^3 points, 32 -> 32 channels with GELU: 145 -> 109 us (201 MB of
+// outputs take 44, the MFMAs 27), 32 -> 5: 100 -> 69, backward data 32 -> 32: 147 -> 125;
+// 8 -> 32: 62 -> 53.  The 8-channel forms have 14 steps and more workgroups a CU; there
+// requests ahead cost registers (backward data 81 -> 103 us) and are left out.
 constexpr int kConvTx = 32, kConvTy = 8;
 constexpr int kConvHx = kConvTx + 2, kConvHy = kConvTy + 2;
 
-template <int EPI, int CPAD>
-__global__ void __launch_bounds__(256) conv_mfma_lds_kernel(const __bf16* __restrict__ in, const __bf16* __restrict__ Wp,
+template <int EPI, int CPAD, bool FRAG>
+__global__ void __launch_bounds__(256, CPAD == 8 ? 3 : 2) conv_mfma_lds_kernel(const __bf16* __restrict__ in, const __bf16* __restrict__ Wp,
                                                             int Kpad, const float* __restrict__ bias, int n,
                                                             float* __restrict__ fout, __bf16* __restrict__ bout,
                                                             const float* __restrict__ pre_in, int ocount, int ostride) {
-    constexpr int LS = CPAD == 32 ? 40 : CPAD;                 // LDS point stride (elements)
-    __shared__ __attribute__((aligned(16))) __bf16 sx[3 * kConvHy * kConvHx * LS];
+    __shared__ __attribute__((aligned(16))) __bf16 sx[3 * kConvHy * kConvHx * CPAD];
+    // element of channel group g (8 channels) of the point (hx, row hr = hz * kConvHy + hy)
+    auto at = [](int hr, int hx, int g) {
+        return (hr * kConvHx + hx) * CPAD + (CPAD == 32 ? (g ^ (hx >> 1 & 3)) * 8 : 0);
+    };
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int row = lane & 31, half = lane >> 5;
@@ -306,36 +318,53 @@ __global__ void __launch_bounds__(256) conv_mfma_lds_kernel(const __bf16* __rest
     const int z = t % n;
     const int64_t b = t / n;
     const __bf16* inb = in + b * P * CPAD;
-    // stage the halo box: 3 x 10 x 34 points, CPAD / 8 16-byte loads each.  A
-    // thread issues all of its loads before its first LDS store, so their
-    // latencies overlap instead of adding up.
-    constexpr int G = CPAD / 8;
-    constexpr int NS = 3 * kConvHy * kConvHx * G;
-    constexpr int IT = (NS + 255) / 256;
-    bf16x8 sv[IT];
+    // stage the halo box: 3 x 10 rows of 34 points, CPAD / 8 16-byte loads each.  A
+    // thread issues all of its loads before its first LDS store, so their latencies
+    // overlap instead of adding up.  Row by row the 32 points of the tile (for CPAD = 32 a
+    // row is the same for a whole wave, its address scalar), then the rows' two end points.
+    constexpr int G = CPAD / 8, ROWS = 3 * kConvHy;
+    constexpr int NM = ROWS * kConvTx * G, NE = ROWS * 2 * G;
+    constexpr int IT = (NM + 255) / 256;
+    static_assert(NE <= 256, "one end load per thread");
+    auto row_base = [&](int hr) {                         // the row's first point
+        const int hz = hr / kConvHy, hy = hr % kConvHy;
+        return inb + ((int64_t)wrapn(z + hz - 1, n) * n + wrapn(y0 + hy - 1, n)) * n * CPAD;
+    };
+    auto row_of = [](int i) {
+        const int r = i / (kConvTx * G);
+        return kConvTx * G >= 64 ? __builtin_amdgcn_readfirstlane(r) : r;
+    };
+    bf16x8 sv[IT], se;
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
         const int i = threadIdx.x + 256 * k;
-        if (i < NS) {
-            const int g = i % G;
-            const int pt = i / G;
-            const int hx = pt % kConvHx, hy = (pt / kConvHx) % kConvHy, hz = pt / (kConvHx * kConvHy);
-            const int gx = wrapn(x0 + hx - 1, n), gy = wrapn(y0 + hy - 1, n), gz = wrapn(z + hz - 1, n);
-            sv[k] = *(const bf16x8*)(inb + (((int64_t)gz * n + gy) * n + gx) * CPAD + g * 8);
-        }
+        if (i < NM) sv[k] = *(const bf16x8*)(row_base(row_of(i)) + x0 * CPAD + i % (kConvTx * G) * 8);
     }
+    const int er = threadIdx.x / (2 * G), ex = threadIdx.x / G % 2 ? kConvHx - 1 : 0;
+    if (threadIdx.x < NE) se = *(const bf16x8*)(row_base(er) + wrapn(x0 + ex - 1, n) * CPAD + threadIdx.x % G * 8);
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
         const int i = threadIdx.x + 256 * k;
-        if (i < NS) *(bf16x8*)(&sx[(i / G) * LS + (i % G) * 8]) = sv[k];
+        if (i < NM) *(bf16x8*)(&sx[at(row_of(i), i / G % kConvTx + 1, i % G)]) = sv[k];
     }
+    if (threadIdx.x < NE) *(bf16x8*)(&sx[at(er, ex, threadIdx.x % G)]) = se;
+    const __bf16* wl = FRAG ? Wp + lane * 8 : Wp + (int64_t)row * Kpad + half * 8;
+    constexpr int WS = FRAG ? 512 : 16;                   // elements from a step's operands to the next's
+    constexpr int kAheadW = CPAD == 32 ? 6 : 0;
+    bf16x8 wv[kAheadW + 1];
+#pragma unroll
+    for (int s = 0; s < kAheadW; ++s) wv[s] = *(const bf16x8*)(wl + s * WS);
     __syncthreads();
     floatx16 acc0 = {0}, acc1 = {0};
-    const __bf16* wrow = Wp + (int64_t)row * Kpad;
     const int ry0 = 2 * wave;                             // tile rows ry0, ry0 + 1 of the two M tiles
-    const int lbase = ry0 * kConvHx + row;                // this lane's point in the halo box, tap (0, 0, 0)
-    // halo-box offset of tap t (dz, dy, dx = t / 9, (t / 3) % 3, t % 3)
-    auto tap_off = [](int t) { return ((t / 9) * kConvHy + (t / 3) % 3) * kConvHx + t % 3; };
+    // this lane's element in the box row ry0 by dx and channel group, each tap a constant from there
+    const __bf16* lx[3][CPAD == 32 ? 2 : 1];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+        for (int c = 0; c < (CPAD == 32 ? 2 : 1); ++c) lx[dx][c] = &sx[at(ry0, row + dx, CPAD == 32 ? 2 * c + half : 0)];
+    constexpr int RS = kConvHx * CPAD;                    // from a box row to the next
+    auto row_off = [](int t) { return ((t / 9) * kConvHy + (t / 3) % 3) * RS; };
     // The K loop runs over the packed width round_up(27 * CPAD, 16) (the value of
     // Kpad) and is unrolled completely, so every tap offset is a constant: a step
     // of 16 kk is one tap (channels c0 .. c0 + 15) for CPAD = 32, two taps (one
@@ -356,30 +385,44 @@ __global__ void __launch_bounds__(256) conv_mfma_lds_kernel(const __bf16* __rest
             }
         }
     }
-#pragma unroll
-    for (int k0 = 0; k0 < KP; k0 += 16) {
-        const bf16x8 bv = *(const bf16x8*)(wrow + k0 + half * 8);
-        bf16x8 a0, a1;
-        const bool valid = CPAD == 32 || k0 / CPAD + half < 27;
-        if (valid) {
-            int po, c;
+    // Operands are requested ahead, weights kAheadW steps (L2 latency), points one step (LDS).
+    auto points = [&](int k0, bf16x8& a0, bf16x8& a1) {
+        if (CPAD == 32 || k0 / CPAD + half < 27) {
+            const __bf16* a;
             if constexpr (CPAD == 32) {
-                po = tap_off(k0 / 32);
-                c = k0 % 32 + half * 8;
+                const int t = k0 / 32;
+                a = lx[t % 3][k0 % 32 / 16] + row_off(t);
             } else {
-                po = half ? tap_off(k0 / CPAD + 1) : tap_off(k0 / CPAD);
-                c = 0;
+                const int t = k0 / CPAD;
+                a = half ? lx[(t + 1) % 3][0] + row_off(t + 1) : lx[t % 3][0] + row_off(t);
             }
-            const int p0 = lbase + po;
-            const int p1 = p0 + kConvHx;                  // next row
-            a0 = *(const bf16x8*)(&sx[p0 * LS + c]);
-            a1 = *(const bf16x8*)(&sx[p1 * LS + c]);
+            a0 = *(const bf16x8*)a;
+            a1 = *(const bf16x8*)(a + RS);                // next row
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j) { a0[j] = (__bf16)0.0f; a1[j] = (__bf16)0.0f; }
         }
-        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, bv, acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bv, acc1, 0, 0, 0);
+    };
+    if constexpr (CPAD == 32) {
+        bf16x8 a0[2], a1[2];
+        points(0, a0[0], a1[0]);
+#pragma unroll
+        for (int s = 0; s < KP / 16; ++s) {
+            if (s + kAheadW < KP / 16) wv[(s + kAheadW) % (kAheadW + 1)] = *(const bf16x8*)(wl + (s + kAheadW) * WS);
+            if (s + 1 < KP / 16) points(16 * (s + 1), a0[(s + 1) & 1], a1[(s + 1) & 1]);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[s & 1], wv[s % (kAheadW + 1)], acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[s & 1], wv[s % (kAheadW + 1)], acc1, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < KP / 16; ++s) {
+            const bf16x8 w = *(const bf16x8*)(wl + s * WS);
+            bf16x8 a0, a1;
+            points(16 * s, a0, a1);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, w, acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, w, acc1, 0, 0, 0);
+        }
     }
     // D[m][o]: o = lane & 31, m = (j / 4) * 8 + (lane >> 5) * 4 + (j & 3); m = x within the row
     const int o = row;
@@ -733,23 +776,26 @@ __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ p, const 
 // Packs one layer's master weights W[o][c][tap] (FP32) into the MFMA layouts:
 //   Wf[o][tap*cpad + c]  (32 x Kf, forward),  Wb[c][tap'*opad + o] (32 x Kb,
 //   backward-data, tap' = 26 - tap mirrors the offset).  Padding entries are 0.
+// frag: in the order of the MFMA operands instead, [kk / 16][kk / 8 % 2][row][kk % 8],
+// 1 KB a step, which a wave loads as one contiguous piece.
 __global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restrict__ W, int cin, int cout, int cpad,
-                                                           int opad, int Kf, int Kb, __bf16* __restrict__ Wf,
+                                                           int opad, int Kf, int Kb, int frag, __bf16* __restrict__ Wf,
                                                            __bf16* __restrict__ Wb) {
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
+    auto at = [&](int row, int kk) { return (kk / 16 * 64 + kk / 8 % 2 * 32 + row) * 8 + kk % 8; };
     if (Wf != nullptr && id < 32 * Kf) {
         const int o = id / Kf, kk = id % Kf;
         const int tap = kk / cpad, c = kk % cpad;
         float v = 0.0f;
         if (o < cout && tap < 27 && c < cin) v = W[(o * cin + c) * 27 + tap];
-        Wf[id] = (__bf16)v;
+        Wf[frag ? at(o, kk) : id] = (__bf16)v;
     }
     if (Wb != nullptr && id < 32 * Kb) {
         const int c = id / Kb, kk = id % Kb;
         const int tapm = kk / opad, o = kk % opad;
         float v = 0.0f;
         if (c < cin && tapm < 27 && o < cout) v = W[(o * cin + c) * 27 + (26 - tapm)];
-        Wb[id] = (__bf16)v;
+        Wb[frag ? at(c, kk) : id] = (__bf16)v;
     }
 }
 
@@ -759,7 +805,7 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restri
 // loads, so it wants many of them in flight on every CU.  A workgroup checks
 // kGuardPer values; the last one to finish (a ticket counter) writes the verdict
 // and clears `state` for the next call.  At 64^3 one workgroup of 1,024 threads
-// took 368 us, 320 workgroups of 4,096 values take about 5 us.
+// took 368 us, 320 workgroups of 4,096 values take about 8 us.
 // state: {values out of bounds seen, workgroups done}, both 0 before the call.
 constexpr int kGuardPer = 4096;   // divides P (a multiple of 32^3)
 __global__ void __launch_bounds__(256) closure_guard_kernel(const float* __restrict__ C, int64_t P,
