@@ -58,8 +58,18 @@ __device__ __forceinline__ CSum csum_merge(CSum a, CSum b) {
 
 constexpr int kDiagQ = 7;          // E_k, enstrophy, 5 conservation sums
 constexpr int kDiagThreads = 256;  // threads of the final reduction
-constexpr int kDiagBlocks = 1024;  // fixed grid: deterministic reduction order
-constexpr int kDiagZ = 32;         // z-planes per work item of the partial kernel
+constexpr int kDiagBlocks = 1024;  // blocks at most; their number and work items follow from the
+                                   // grid size alone: deterministic reduction order
+constexpr int kDiagZ = 32;         // z-planes per work item of the partial kernel at most
+
+// Planes per work item: kDiagZ where that makes an item for every block, else as few as
+// give each block one.  An item's planes are one serial chain: at 32^3, order 4, four
+// items of 32 planes took 82 us, 128 of one plane take 12.
+inline int diag_planes(int tiles, int nz) {
+    const int chunks = kDiagBlocks / tiles > 1 ? kDiagBlocks / tiles : 1;
+    const int dz = (nz + chunks - 1) / chunks;
+    return dz < kDiagZ ? dz : kDiagZ;
+}
 
 // Doubles of LDS the block reduction of NT threads needs.
 template <int NT>
@@ -113,7 +123,7 @@ struct DiagShape {
 // double before any arithmetic.  Vorticity uses the order-2R central first
 // derivative with weights da (a_m / h, double) of u = m / rho, each taken with
 // one IEEE division per point.  A block takes work items (a tile of columns and
-// a chunk of kDiagZ planes) in a fixed round-robin order and marches each in z:
+// a chunk of dz planes) in a fixed round-robin order and marches each in z:
 // (u0, u1) of the tile's columns over the last 2R+1 planes and u2 over the last
 // R+1 (only the centre plane's is differentiated) sit in LDS rings, and the
 // tangential components of the centre plane's x and y rings are loaded per plane.
@@ -121,7 +131,7 @@ struct DiagShape {
 // (as doubles).
 template <typename T, int R>
 __global__ void __launch_bounds__(DiagShape<R>::NT, DiagShape<R>::MINW) diag_partial_kernel(const T* __restrict__ q, int nx, int ny, int nz,
-                                                                        const double* __restrict__ da, double gm1,
+                                                                        int dz, const double* __restrict__ da, double gm1,
                                                                         int symx, int symy, int symz,
                                                                         double* __restrict__ part) {
     using S = DiagShape<R>;
@@ -147,11 +157,11 @@ __global__ void __launch_bounds__(DiagShape<R>::NT, DiagShape<R>::MINW) diag_par
     unsigned cnt[3] = {0u, 0u, 0u};
 
     const int tiles_x = (nx + TX - 1) / TX, tiles_y = (ny + TY - 1) / TY;
-    const int items = tiles_x * tiles_y * ((nz + kDiagZ - 1) / kDiagZ);
+    const int items = tiles_x * tiles_y * ((nz + dz - 1) / dz);
     for (int it = blockIdx.x; it < items; it += gridDim.x) {
         const int tile = it % (tiles_x * tiles_y), chunk = it / (tiles_x * tiles_y);
         const int x0 = (tile % tiles_x) * TX, y0 = (tile / tiles_x) * TY;
-        const int z0 = chunk * kDiagZ, z1 = min(nz, z0 + kDiagZ);
+        const int z0 = chunk * dz, z1 = min(nz, z0 + dz);
         unsigned f;
         // the tile's columns as a window of the wrapped (or mirrored) box: a
         // column beyond the box holds the values of the point it folds onto

@@ -462,21 +462,30 @@ extern "C" int sbli_rk3_step(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
 extern "C" int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]) {
     if (!ctx) return fail(nullptr, SBLI_ERR_ARG, "sbli_diagnostics: ctx is NULL");
     if (!q || !out) return fail(ctx, SBLI_ERR_ARG, "sbli_diagnostics: NULL pointer");
-    const int nb = kDiagBlocks;
+    int nb = kDiagBlocks;
     const double gm1 = ctx->p.gamma - 1.0;
     const int r = ctx->r;
-#define DIAG_LAUNCH(T, RR)                                                                                      \
-    diag_partial_kernel<T, RR><<<nb, DiagShape<RR>::NT, 0, ctx->stream>>>((const T*)q, ctx->p.nx, ctx->p.ny, ctx->p.nz, \
-                                                                     ctx->diag_da, gm1, ctx->p.bc[0], ctx->p.bc[1], \
-                                                                     ctx->p.bc[2], ctx->diag_part)
+    auto split = [&](int TX, int TY) {   // planes per work item; nb: no block without one
+        const int64_t tiles = (int64_t)((ctx->p.nx + TX - 1) / TX) * ((ctx->p.ny + TY - 1) / TY);
+        const int dz = diag_planes((int)std::min<int64_t>(tiles, kDiagBlocks), ctx->p.nz);
+        nb = (int)std::min<int64_t>(kDiagBlocks, tiles * ((ctx->p.nz + dz - 1) / dz));
+        return dz;
+    };
+#define DIAG_LAUNCH(T, RR)                                                                                          \
+    {                                                                                                               \
+        const int dz = split(DiagShape<RR>::TX, DiagShape<RR>::TY);                                                 \
+        diag_partial_kernel<T, RR><<<nb, DiagShape<RR>::NT, 0, ctx->stream>>>(                                      \
+            (const T*)q, ctx->p.nx, ctx->p.ny, ctx->p.nz, dz, ctx->diag_da, gm1, ctx->p.bc[0], ctx->p.bc[1],        \
+            ctx->p.bc[2], ctx->diag_part);                                                                          \
+    }
     if (ctx->p.dtype == SBLI_F64) {
-        if (r == 1) DIAG_LAUNCH(double, 1); else if (r == 2) DIAG_LAUNCH(double, 2);
-        else if (r == 3) DIAG_LAUNCH(double, 3); else if (r == 4) DIAG_LAUNCH(double, 4);
-        else if (r == 5) DIAG_LAUNCH(double, 5); else DIAG_LAUNCH(double, 6);
+        if (r == 1) DIAG_LAUNCH(double, 1) else if (r == 2) DIAG_LAUNCH(double, 2)
+        else if (r == 3) DIAG_LAUNCH(double, 3) else if (r == 4) DIAG_LAUNCH(double, 4)
+        else if (r == 5) DIAG_LAUNCH(double, 5) else DIAG_LAUNCH(double, 6)
     } else {
-        if (r == 1) DIAG_LAUNCH(float, 1); else if (r == 2) DIAG_LAUNCH(float, 2);
-        else if (r == 3) DIAG_LAUNCH(float, 3); else if (r == 4) DIAG_LAUNCH(float, 4);
-        else if (r == 5) DIAG_LAUNCH(float, 5); else DIAG_LAUNCH(float, 6);
+        if (r == 1) DIAG_LAUNCH(float, 1) else if (r == 2) DIAG_LAUNCH(float, 2)
+        else if (r == 3) DIAG_LAUNCH(float, 3) else if (r == 4) DIAG_LAUNCH(float, 4)
+        else if (r == 5) DIAG_LAUNCH(float, 5) else DIAG_LAUNCH(float, 6)
     }
 #undef DIAG_LAUNCH
     HIP_TRY(ctx, hipGetLastError());
