@@ -205,10 +205,10 @@ static void choose_fused(int dtype, int r, const sbli_params* p, int count, int*
 
 // Where the staged form is the default.  Order 8, and order 6 in FP64: it is the faster
 // one on every grid (us a stage, fused in its best configuration against staged: FP64
-// order 6, 32^3: 25, 20; 64^3: 64, 32; 128^3: 377, 184; 256^3: 2,998, 1,369; FP32 order 8:
-// 27, 16; 50, 26; 221, 123; 1,629, 976).  FP32 order 6: up to about 96^3 (17, 15; 27, 24;
-// 96^3: 55, 55; 128^3: 93, 116; 256^3: 637, 911).  Not at orders 2 and 4 (FP64 order 4:
-// 12, 17; 24, 28; 91, 164; 654, 1,236).  Its scratch is allocated with the context, so a
+// order 6, 32^3: 25, 14; 64^3: 64, 28; 128^3: 377, 147; 256^3: 2,998, 1,042; FP32 order 8:
+// 27, 13; 50, 23; 221, 119; 1,629, 772).  FP32 order 6: up to about 96^3 (17, 13; 27, 21;
+// 96^3: 55, 46; 128^3: 93, 102; 256^3: 612, 770).  Not at orders 2 and 4 (FP64 order 4:
+// 12, 13; 23, 25; 91, 166; 592, 1,230).  Its scratch is allocated with the context, so a
 // grid only defaults to it while that is a small part of the free memory: a program that
 // fills the device with states is not made to run out of it.
 static bool prefers_staged(const sbli_params* p, int r) {

@@ -40,11 +40,8 @@ static void staged_run(const StagedArgs& a, const T* qin, T* dq, T* qout, T* nf)
         const int64_t units = (int64_t)tiles * ((c.n[2] + zc - 1) / zc);
         return (unsigned)(kStagedXcds * ((units + kStagedXcds - 1) / kStagedXcds));
     };
-    {
-        // The nested-field step in 32x32 tiles where the register and LDS budget allows
-        // (every radius in FP32, up to R = 4 in FP64): each tile then fetches its R-wide
-        // x-arms, 32-byte row pieces of 128-byte lines, for four times as many own points.
-        constexpr int TN = (sizeof(T) == 8 && R > 4) ? kStagedTile : 2 * kStagedTile;
+    auto nested = [&](auto tn) {
+        constexpr int TN = decltype(tn)::value;
         const int tx = (c.n[0] + TN - 1) / TN, ty = (c.n[1] + TN - 1) / TN;
         // Both steps, us a stage, runs of 64 -> this: 32^3, FP64, order 8: 100 -> 22; 64^3:
         // 222 -> 36; 96^3: 268 -> 92; 128^3: 379 -> 198; 160^3: 514 -> 377; 256^3 keeps 64.
@@ -56,7 +53,20 @@ static void staged_run(const StagedArgs& a, const T* qin, T* dq, T* qout, T* nf)
         else
             staged_nested_zring_kernel<T, R, TN, false><<<grid_of(tx * ty, zn), TN * TN, 0, a.stream>>>(qin, nf, c, tx,
                                                                                                          ty, zn);
-    }
+    };
+    // The nested-field step in 32x32 tiles where the register and LDS budget allows
+    // (every radius in FP32, up to R = 4 in FP64): each tile then fetches its R-wide
+    // x-arms, 32-byte row pieces of 128-byte lines, for four times as many own points.
+    // In 16x16 tiles on grids whose 32x32 tiles, plane by plane, are no more than the CUs
+    // (up to 64^3): both steps, FP64 order 8, 32^3 21.8 -> 16.4 us, 64^3 35.4 -> 32.0, but
+    // 96^3 70.6 -> 72.5 and 256^3 1,150 -> 1,184; FP32 16.2 -> 13.6, 26.1 -> 23.7, 57.1 ->
+    // 60.9, 776 -> 840.
+    constexpr bool kWide = sizeof(T) == 4 || R <= 4;
+    const int64_t wide_units = (int64_t)((c.n[0] + 31) / 32) * ((c.n[1] + 31) / 32) * c.n[2];
+    if (kWide && wide_units > 256)
+        nested(std::integral_constant<int, kWide ? 2 * kStagedTile : kStagedTile>{});
+    else
+        nested(std::integral_constant<int, kStagedTile>{});
     const int tx = (c.n[0] + kStagedTile - 1) / kStagedTile, ty = (c.n[1] + kStagedTile - 1) / kStagedTile;
     constexpr int NT = kStagedTile * kStagedTile;
     const T dt = (T)a.dt, A = (T)a.A, B = (T)a.B;
