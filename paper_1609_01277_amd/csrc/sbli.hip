@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -41,6 +42,8 @@ struct sbli_ctx {
     double* diag_da;        // 3 * kMaxR weights a_m / h (double) for the vorticity
     double* diag_out;       // 10 doubles
     void* stg;              // scratch of the staged form (kStagedScratchWords * P elements) or null
+    std::mutex stg_pair;    // held while the staged form's two launches are enqueued: calls from
+                            // several threads then use the scratch one after the other
     std::string err;
 };
 
@@ -388,6 +391,7 @@ static int launch_any(sbli_ctx* ctx, const void* qin, void* dq, void* qout, int 
         const bool f64 = ctx->p.dtype == SBLI_F64;
         const StagedArgs a{ctx->stream, f64, ctx->r, f64 ? (const void*)&ctx->c64 : (const void*)&ctx->c32,
                            ctx->stg, mode, dt, A, B, ctx->net ? ctx->clos : nullptr, ctx->net ? ctx->cflag : nullptr};
+        std::lock_guard<std::mutex> pair(ctx->stg_pair);
         staged_launch(a, qin, dq, qout);
         return SBLI_OK;
     }
