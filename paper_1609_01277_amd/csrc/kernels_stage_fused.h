@@ -1199,6 +1199,7 @@ struct BoxInst {
 };
 
 constexpr int kStripRows = 4;   // tile rows of a strip (see fused_stage_kernel)
+constexpr int kXcdPiece = 16;   // workgroups of an ensemble dealt to an XCD at a time
 
 // Threads of a workgroup: schedule 2 has as many plane threads as column threads.
 template <int R, int TX, int TY, int DB>
@@ -1221,8 +1222,14 @@ __global__ void __launch_bounds__((fused_threads<R, TX, TY, DB>()), MINW)
                        const BoxInst<T>* __restrict__ inst, int ninst, T dt_scale, T A, T B) {
     const int total = gridDim.x;
     const int w = blockIdx.x;
-    const int xcd = w % 8, per = total / 8, extra = total % 8;   // the first `extra` XCDs take one more
-    const int lam = xcd * per + min(xcd, extra) + w / 8;
+    const int xcd = w % 8;
+    // An ensemble's workgroups differ in length: its XCDs take turns in pieces of kXcdPiece
+    // neighbours, and only what is left over goes in eighths.
+    const int dealt = ninst > 1 ? total / (8 * kXcdPiece) * (8 * kXcdPiece) : 0;
+    const int per = (total - dealt) / 8, extra = total % 8;      // the first `extra` XCDs take one more
+    const int turn = w / 8;
+    const int lam = w < dealt ? (turn / kXcdPiece * 8 + xcd) * kXcdPiece + turn % kXcdPiece
+                              : dealt + xcd * per + min(xcd, extra) + (turn - dealt / 8);
     int lo = 0, hi = ninst - 1;     // last box with first_wg <= lam
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
