@@ -423,16 +423,22 @@ template <typename Tin>
 static void box_filter_launch(hipStream_t s, const Tin* fine, int nf, int nfields, int ratio, float* coarse,
                               int subtract) {
     const int nc = nf / ratio;
-    const dim3 grid((nc + 63) / 64, (nc + kFilterWaves - 1) / kFilterWaves,
-                    (unsigned)nfields * ((nc + kFilterZ - 1) / kFilterZ));
-    const bool rows = (uintptr_t)fine % 16 == 0 && grid.y <= 65535 &&
-                      (int64_t)nfields * ((nc + kFilterZ - 1) / kFilterZ) <= 65535;
+    // Output planes of a workgroup: kFilterZ, fewer where that leaves the chip short of five
+    // workgroups a CU (the fine plane that two outputs share is then read twice more often).
+    // Five FP64 fields, us with 4 / 2 / 1: 256^3 by 4: 133 / 150 / 163, 128^3 by 4: 36 / 23 /
+    // 21, 240^3 by 8: 240 / 170 / 164, 72^3 by 4: 17 / 12 / 10.
+    const int64_t across = (int64_t)((nc + 63) / 64) * ((nc + kFilterWaves - 1) / kFilterWaves) * nfields;
+    int zper = kFilterZ;
+    while (zper > 1 && across * ((nc + zper - 1) / zper) < 5 * 256) zper /= 2;
+    const int64_t gz = (int64_t)nfields * ((nc + zper - 1) / zper);
+    const dim3 grid((nc + 63) / 64, (nc + kFilterWaves - 1) / kFilterWaves, (unsigned)gz);
+    const bool rows = (uintptr_t)fine % 16 == 0 && grid.y <= 65535 && gz <= 65535;
     if (rows && ratio == 2)
-        box_filter_rows_kernel<Tin, 2><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract);
+        box_filter_rows_kernel<Tin, 2><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract, zper);
     else if (rows && ratio == 4)
-        box_filter_rows_kernel<Tin, 4><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract);
+        box_filter_rows_kernel<Tin, 4><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract, zper);
     else if (rows && ratio == 8)
-        box_filter_rows_kernel<Tin, 8><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract);
+        box_filter_rows_kernel<Tin, 8><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract, zper);
     else
         box_filter_kernel<Tin><<<nblk((int64_t)nc * nc * nc * nfields), 256, 0, s>>>(fine, nf, nfields, ratio, coarse,
                                                                                      subtract);

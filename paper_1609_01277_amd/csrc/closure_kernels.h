@@ -73,15 +73,20 @@ __global__ void __launch_bounds__(256) box_filter_kernel(const Tin* __restrict__
 // (671 MB), most of it in strided loads.  Here a lane loads the `ratio` consecutive
 // values from its own point on (16-byte loads, a wavefront covers one contiguous run
 // of a row) and takes the ratio/2 values to its left from the lane below; a thread
-// marches kFilterZ output planes, and the z-plane two outputs share is reduced once.
-// About 175 us.  The sums run in the order of box_filter_kernel, so the results are the
+// marches zper output planes, and the z-plane two outputs share is reduced once.  The rows
+// of one fine plane are requested together (three at a time for ratio 8), the planes one
+// after the other: with several planes unrolled the registers leave two wavefronts a SIMD
+// (ratio 4, FP64: 223 VGPRs, 171 us; 80 now) or spill (ratio 8).  133 us at 256^3, 5.0 TB/s
+// (reads alone reach 5.9); 240^3 by 8: 264 -> 164 us; 200^3 by 2: 146 -> 90; 512^3 by 8:
+// 3,859 -> 964.  The sums run in the order of box_filter_kernel, so the results are the
 // same bits.
-constexpr int kFilterZ = 4;      // output planes of a workgroup: 4 ratio + 1 fine planes
+constexpr int kFilterZ = 4;      // output planes of a workgroup at most: 4 ratio + 1 fine planes
 constexpr int kFilterWaves = 4;  // output rows of a workgroup
 template <typename Tin, int RATIO>
 __global__ void __launch_bounds__(64 * kFilterWaves)
-    box_filter_rows_kernel(const Tin* __restrict__ fine, int nf, float* __restrict__ coarse, int subtract) {
+    box_filter_rows_kernel(const Tin* __restrict__ fine, int nf, float* __restrict__ coarse, int subtract, int zper) {
     constexpr int H = RATIO / 2;
+    constexpr int kRows = RATIO == 8 ? 3 : RATIO + 1;   // rows requested together
     constexpr int VL = 16 / (int)sizeof(Tin) < RATIO ? 16 / (int)sizeof(Tin) : RATIO;   // values of one load
     typedef Tin Vec __attribute__((ext_vector_type(VL)));
     const int nc = nf / RATIO;
@@ -89,8 +94,8 @@ __global__ void __launch_bounds__(64 * kFilterWaves)
     const int lane = threadIdx.x & 63;
     const int xc = blockIdx.x * 64 + lane;
     const int yc = blockIdx.y * kFilterWaves + (threadIdx.x >> 6);
-    const int nzb = (nc + kFilterZ - 1) / kFilterZ;
-    const int f = blockIdx.z / nzb, zc0 = (blockIdx.z % nzb) * kFilterZ;
+    const int nzb = (nc + zper - 1) / zper;
+    const int f = blockIdx.z / nzb, zc0 = (blockIdx.z % nzb) * zper;
     if (yc >= nc) return;                              // a whole wavefront
     const int xl = xc < nc ? xc : nc - 1;              // lanes beyond the row repeat its last point
     const double wi = 1.0 / RATIO, we = 0.5 / RATIO;
@@ -123,19 +128,19 @@ __global__ void __launch_bounds__(64 * kFilterWaves)
     auto ysum = [&](int z) {
         const Tin* pz = src + (int64_t)wrapn(z, nf) * nf * nf;
         double acc = 0.0;
-#pragma unroll
+#pragma unroll kRows
         for (int dy = -H; dy <= H; ++dy) {
             const double wy = (dy == -H || dy == H) ? we : wi;
             acc += wy * xsum(pz + (int64_t)wrapn(yc * RATIO + dy, nf) * nf);
         }
         return acc;
     };
-    const int zc1 = min(zc0 + kFilterZ, nc);
+    const int zc1 = min(zc0 + zper, nc);
     double shared_plane = ysum(zc0 * RATIO - H);       // the plane this output shares with the one below
     for (int zc = zc0; zc < zc1; ++zc) {
         double acc = 0.0;
         acc += we * shared_plane;
-#pragma unroll
+#pragma unroll 1
         for (int dz = -H + 1; dz <= H; ++dz) {
             const double s = ysum(zc * RATIO + dz);
             acc += (dz == H ? we : wi) * s;
