@@ -62,9 +62,10 @@ struct FusedShape {
 // Point fields kept per plane and per column.
 template <typename T>
 struct PF {
-    // ei = rho E - rho u_j u_j / 2, so p = (gamma - 1) ei; Th = (gamma / Pr) ei / rho, the
-    // temperature scaled so that the heat flux is (1/Re) grad Th.  (kPlain: p and T.)
-    T rho, m0, m1, m2, E, u0, u1, u2, ei, Th;
+    // pk = -(gamma - 1) rho u_j u_j, so 2p = 2 (gamma - 1) rho E + pk; Th = (gamma / Pr) times
+    // the internal energy, the temperature scaled so that the heat flux is (1/Re) grad Th.
+    // (kPlain: p and T.)
+    T rho, m0, m1, m2, E, u0, u1, u2, pk, Th;
 };
 
 // 1/x from the hardware reciprocal refined by Newton steps (two in FP64, one in
@@ -98,6 +99,18 @@ __device__ __forceinline__ float fmaT(float a, float b, float c) { return __buil
 template <typename T, int MODE>
 constexpr bool kPlain = sizeof(T) == 4 && MODE == kModeRHS;
 
+// Velocity component m / rho, rr = fast_recip(rho).  Every field's residual inherits the
+// rounding of u, so outside the plain formulation one residual step makes it the rounded
+// quotient: two operations a component, for an error of the mass residual of 0.8 times
+// (FP64, order 4) and of the energy residual of 0.65 times that of the plain formulation
+// (1.02 and 0.86 without the step).
+template <bool PLAIN, typename T>
+__device__ __forceinline__ T velocity(T m, T rho, T rr) {
+    const T u = m * rr;
+    if constexpr (PLAIN) return u;
+    else return fmaT(fmaT(-rho, u, m), rr, u);
+}
+
 template <typename T, bool PLAIN>
 __device__ __forceinline__ PF<T> make_pf(T rho, T m0, T m1, T m2, T E, const BoxConst<T>& c) {
     PF<T> s;
@@ -107,16 +120,16 @@ __device__ __forceinline__ PF<T> make_pf(T rho, T m0, T m1, T m2, T E, const Box
     s.m2 = m2;
     s.E = E;
     const T rr = fast_recip(rho);
-    s.u0 = m0 * rr;
-    s.u1 = m1 * rr;
-    s.u2 = m2 * rr;
+    s.u0 = velocity<PLAIN>(m0, rho, rr);
+    s.u1 = velocity<PLAIN>(m1, rho, rr);
+    s.u2 = velocity<PLAIN>(m2, rho, rr);
     const T ke2 = fmaT(m2, s.u2, fmaT(m1, s.u1, m0 * s.u0));    // 2 x kinetic energy
     if constexpr (PLAIN) {
-        s.ei = c.gm1 * fmaT(T(-0.5), ke2, E);
-        s.Th = c.gM2 * s.ei * rr;
+        s.pk = c.gm1 * fmaT(T(-0.5), ke2, E);
+        s.Th = c.gM2 * s.pk * rr;
     } else {
-        s.ei = fmaT(T(-0.5), ke2, E);
-        s.Th = c.gPr * s.ei * rr;
+        s.pk = -(c.gm1 * ke2);
+        s.Th = c.gPr * fmaT(T(-0.5), ke2, E) * rr;
     }
     return s;
 }
@@ -125,7 +138,7 @@ __device__ __forceinline__ PF<T> make_pf(T rho, T m0, T m1, T m2, T E, const Box
 // (the same operations as in make_pf): the register windows need not hold it.
 template <bool PLAIN, typename T>
 __device__ __forceinline__ PF<T> with_pressure(PF<T> s, const BoxConst<T>& c) {
-    if constexpr (PLAIN) s.ei = c.gm1 * fmaT(T(-0.5), fmaT(s.m2, s.u2, fmaT(s.m1, s.u1, s.m0 * s.u0)), s.E);
+    if constexpr (PLAIN) s.pk = c.gm1 * fmaT(T(-0.5), fmaT(s.m2, s.u2, fmaT(s.m1, s.u1, s.m0 * s.u0)), s.E);
     return s;
 }
 
@@ -170,7 +183,10 @@ __device__ __forceinline__ int wrap_mod(int v, int n) {
 
 // Whether the momentum of a point is kept in LDS beside rho and u.  In FP64 the LDS
 // pipe is the busier one (44 % against 34 % for the VALU at order 4, 512^3), and
-// x and y neighbours form rho u_i again; in FP32, with half the bytes, the VALU is.
+// x and y neighbours form the momentum across the axis as rho u_i again; in FP32, with
+// half the bytes, the VALU is.  The momentum along the axis is always the state's own: in
+// the mass residual D_j (rho u_j) carries the rounding of rho u_j in full, and with rho
+// times the rounded u_j that residual's error was 1.7 to 2.0 times the plain formulation's.
 template <typename T>
 constexpr bool kMomentumInLds = sizeof(T) == 4;
 // LDS fields of a plane beside u: rho, rho E, Th, the momentum where it is kept, and the
@@ -180,24 +196,25 @@ constexpr int kPlFields = (kMomentumInLds<T> ? 6 : 3) + (PLAIN ? 1 : 0);
 // Fields of a plane below the output plane in LDS (ZL; FP64 only): rho, rho u_i, rho E, u_i, Th.
 constexpr int kZtFields = 9;
 
-// The centre point of the x and y sums: its momentum is formed like the neighbours'.
-template <typename T>
-__device__ __forceinline__ PF<T> centre_xy(PF<T> s) {
+// A point of the sums along axis d: s.m_d is the state's, the others are formed from u
+// (the centre point like its neighbours).
+template <int d, typename T>
+__device__ __forceinline__ PF<T> point_along(PF<T> s) {
     if constexpr (!kMomentumInLds<T>) {
-        s.m0 = s.rho * s.u0;
-        s.m1 = s.rho * s.u1;
-        s.m2 = s.rho * s.u2;
+        if constexpr (d != 0) s.m0 = s.rho * s.u0;
+        if constexpr (d != 1) s.m1 = s.rho * s.u1;
+        if constexpr (d != 2) s.m2 = s.rho * s.u2;
     }
     return s;
 }
 
-// FP64 at orders 6 and up: the z sums form the momentum likewise, rho u at the point and
-// its neighbours, so that a register window of 2R + 1 planes need not hold it.
+// FP64 at orders 6 and up: the z sums form the momentum across the axis likewise, so that
+// a register window of 2R + 1 planes need not hold it.
 template <typename T, int R>
 constexpr bool kMomentumFromU = !kMomentumInLds<T> && R >= 3;
 template <typename T, int R>
 __device__ __forceinline__ PF<T> z_point(PF<T> s) {
-    if constexpr (kMomentumFromU<T, R>) return centre_xy(s);
+    if constexpr (kMomentumFromU<T, R>) return point_along<2>(s);
     return s;
 }
 
@@ -205,7 +222,9 @@ __device__ __forceinline__ PF<T> z_point(PF<T> s) {
 // (g_ij = D_j u_i, theta = g_kk).  With the point's pressure they become the two
 // fields whose first derivatives enter the residual:
 //   W_j = 2 (u_i tau_ij - p u_j)  (energy)    G_j = 2 p - 2 (theta - g_jj) / (3 Re)  (momentum j)
-// so the pressure terms cost a stencil nothing.  G is rounded once from 2 (gamma - 1) ei.
+// so the pressure terms cost a stencil nothing.  2p is taken from rho E and pk each time, so
+// G is rounded once at the size of 2p where p from the internal energy is rounded twice: the
+// momentum residual's error is 0.6 to 0.8 times the plain formulation's.
 // PLAIN: V_j = u_i tau_ij and t_j = theta - g_jj themselves, W = V, G = t.
 template <bool PLAIN, typename T>
 __device__ __forceinline__ void nested_terms(const T (&g)[3][3], T u0, T u1, T u2, const BoxConst<T>& c, T (&V)[3],
@@ -236,12 +255,12 @@ __device__ __forceinline__ void nested_terms(const T (&g)[3][3], T u0, T u1, T u
     }
 }
 template <bool PLAIN, typename T>
-__device__ __forceinline__ T nested_W(T V, T ei, T u, const BoxConst<T>& c) {
-    return PLAIN ? V : fmaT(c.inv_Re2, V, -((c.gm1x2 * ei) * u));
+__device__ __forceinline__ T nested_W(T V, const PF<T>& s, T u, const BoxConst<T>& c) {
+    return PLAIN ? V : fmaT(c.inv_Re2, V, -(fmaT(c.gm1x2, s.E, s.pk) * u));
 }
 template <bool PLAIN, typename T>
-__device__ __forceinline__ T nested_G(T t, T ei, const BoxConst<T>& c) {
-    return PLAIN ? t : fmaT(c.gm1x2, ei, t);
+__device__ __forceinline__ T nested_G(T t, const PF<T>& s, const BoxConst<T>& c) {
+    return PLAIN ? t : fmaT(c.gm1x2, s.E, s.pk + t);
 }
 
 // -2 times the residual of one point, summed neighbour pair by neighbour pair.
@@ -250,11 +269,15 @@ __device__ __forceinline__ T nested_G(T t, T ei, const BoxConst<T>& c) {
 // linearity of D, -1/2 [D(Q u) + Q D u + u D Q] = -1/2 sum_m a_m/h [(Q + Q+)(u + u+) -
 // (Q + Q-)(u + u-)], and each bracket is (Q + Q+)(u+ - u-) + (Q+ - Q-)(u + u-): differences
 // of neighbours are taken before any product, and the three terms of every field cost two
-// additions and two fused multiply-adds a pair.  Every sum goes straight into the residual
-// (the weights hold the coefficients), so a direction ends without a combining step:
-// 37 operations a pair, where separate sums of the derivatives of Q, Q u, u, p, theta and V
-// took 41 a pair and 27 a direction.  The factor -2 is exact and saves a second set of
-// weights.
+// additions and two fused multiply-adds a pair.  For Q = rho, Q u is the momentum itself, an
+// input: there the pair's term is (rho u+ - rho u-) + u (Q+ - Q-) + Q (u+ - u-), in which u's
+// rounding enters once (in the bracket, where Q u is formed from u, twice).  Every sum goes
+// straight into the residual (the weights hold the coefficients), so a direction ends
+// without a combining step: 38 operations a pair, where separate sums of the derivatives of
+// Q, Q u, u, p, theta and V took 41 a pair and 27 a direction.  The factor -2 is exact and
+// saves a second set of weights.  RMS error against 113-bit arithmetic over that of those
+// separate sums, orders 2 to 12, both types: mass 0.76 to 0.86, momentum 0.60 to 0.81,
+// energy 0.64 to 0.70.
 template <typename T, bool PLAIN>
 struct ResidualSums {
     T Rr, R0, R1, R2, RE;
@@ -291,9 +314,11 @@ struct ResidualSums {
         const T ua = d == 0 ? a.u0 : (d == 1 ? a.u1 : a.u2);
         const T ub = d == 0 ? b.u0 : (d == 1 ? b.u1 : b.u2);
         const T w = c.da[d][mi], v = c.v2[d][mi], vn = c.v2n[d][mi];
-        const T wd = w * (ua - ub), ws = w * (uc + ub);
+        const T ma = d == 0 ? a.m0 : (d == 1 ? a.m1 : a.m2);
+        const T mb = d == 0 ? b.m0 : (d == 1 ? b.m1 : b.m2);
+        const T du = ua - ub, wd = w * du, ws = w * (uc + ub);
         auto conv = [&](T qc, T qa, T qb, T r) { return fmaT(qa - qb, ws, fmaT(qc + qa, wd, r)); };
-        Rr = conv(s.rho, a.rho, b.rho, Rr);
+        Rr = fmaT(w, fmaT(s.rho, du, fmaT(uc, a.rho - b.rho, ma - mb)), Rr);
         R0 = conv(s.m0, a.m0, b.m0, R0);
         R1 = conv(s.m1, a.m1, b.m1, R1);
         R2 = conv(s.m2, a.m2, b.m2, R2);
@@ -335,7 +360,7 @@ struct DirSums {
         dM1 = fmaT(w, a.m1 - b.m1, dM1);
         dM2 = fmaT(w, a.m2 - b.m2, dM2);
         // momentum fluxes rho u_i u_d (+ 2p for i = d): differences a - b
-        const T pa2 = T(2) * (a.ei - b.ei);
+        const T pa2 = T(2) * (a.pk - b.pk);
         const T f0 = d == 0 ? fmaT(a.m0, ua, pa2 - b.m0 * ub) : fmaT(a.m0, ua, -(b.m0 * ub));
         const T f1 = d == 1 ? fmaT(a.m1, ua, pa2 - b.m1 * ub) : fmaT(a.m1, ua, -(b.m1 * ub));
         const T f2 = d == 2 ? fmaT(a.m2, ua, pa2 - b.m2 * ub) : fmaT(a.m2, ua, -(b.m2 * ub));
@@ -344,8 +369,8 @@ struct DirSums {
         dF2 = fmaT(w, f2, dF2);
         dE = fmaT(w, a.E - b.E, dE);
         // energy flux (rho E + 2p) u_d - 2 V_d: difference a - b
-        const T hb = fmaT(fmaT(T(2), b.ei, b.E), ub, T(-2) * Vb);
-        const T fh = fmaT(fmaT(T(2), a.ei, a.E), ua, fmaT(T(-2), Va, -hb));
+        const T hb = fmaT(fmaT(T(2), b.pk, b.E), ub, T(-2) * Vb);
+        const T fh = fmaT(fmaT(T(2), a.pk, a.E), ua, fmaT(T(-2), Va, -hb));
         dH = fmaT(w, fh, dH);
         dU = fmaT(w, ua - ub, dU);
         dTh = fmaT(w, Tha - Thb, dTh);
@@ -416,6 +441,14 @@ struct ResidualSums<T, true> {
     }
 };
 
+// The scheduler keeps to one neighbour pair of the sums at a time.  Left alone, in FP64 it
+// requests every pair's LDS reads first, and the threads of fused_stage_body spill 27 to 92
+// registers (their window takes about 130 of 256); the plane wavefronts of the split form
+// spill none either way, but their residual alone takes 545 us instead of 527 (256^3, order 4).
+__device__ __forceinline__ void pair_fence() {
+    __builtin_amdgcn_sched_barrier(0x100);   // LDS reads may cross
+}
+
 // One workgroup = one (x, y) tile and one z-chunk [z0, z0 + zc).
 // PRE: whether the state of the entering plane and of the u-ring point is
 // requested one iteration ahead (1) or in the iteration itself (0).  RT = 1
@@ -433,6 +466,9 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
     constexpr int NW = DB ? 2 : 1;     // buffers of its nested pairs
     __shared__ T s_u[NP][3][S::BY2][S::BX2];
     __shared__ T s_pl[NP][kPlFields<T, PL>][S::BY1][S::BX1];
+    // FP64: rho u_0 of the tile's rows and rho u_1 of its columns, with their R-ring
+    __shared__ T s_mx[kMomentumInLds<T> ? 1 : NP][kMomentumInLds<T> ? 1 : TY][kMomentumInLds<T> ? 1 : TX + 2 * R];
+    __shared__ T s_my[kMomentumInLds<T> ? 1 : NP][kMomentumInLds<T> ? 1 : TY + 2 * R][kMomentumInLds<T> ? 1 : TX];
     // (W_x, G_x, W_y, G_y) of a gradient plane over the tile and its R-ring
     __shared__ T s_xy[NW][4][S::BY1][S::BX1];
     // (W_z, G_z) of the last 2R+1 gradient planes over the tile, indexed by iteration
@@ -608,14 +644,17 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
                         s_pl[bp][3][cy + R][cx + R] = f.m0;
                         s_pl[bp][4][cy + R][cx + R] = f.m1;
                         s_pl[bp][5][cy + R][cx + R] = f.m2;
+                    } else {
+                        if (cy >= 0 && cy < TY) s_mx[bp][cy][cx + R] = f.m0;
+                        if (cx >= 0 && cx < TX) s_my[bp][cy + R][cx] = f.m1;
                     }
-                    if constexpr (PL) s_pl[bp][kPlFields<T, PL> - 1][cy + R][cx + R] = with_pressure<PL>(f, c).ei;
+                    if constexpr (PL) s_pl[bp][kPlFields<T, PL> - 1][cy + R][cx + R] = with_pressure<PL>(f, c).pk;
                 }
                 if (has_out) {
                     const T rr = fast_recip(cr0);
-                    s_u[bp][0][oy + 2 * R][ox + 2 * R] = cr1 * rr;
-                    s_u[bp][1][oy + 2 * R][ox + 2 * R] = cr2 * rr;
-                    s_u[bp][2][oy + 2 * R][ox + 2 * R] = cr3 * rr;
+                    s_u[bp][0][oy + 2 * R][ox + 2 * R] = velocity<PL>(cr1, cr0, rr);
+                    s_u[bp][1][oy + 2 * R][ox + 2 * R] = velocity<PL>(cr2, cr0, rr);
+                    s_u[bp][2][oy + 2 * R][ox + 2 * R] = velocity<PL>(cr3, cr0, rr);
                 }
             }
             __syncthreads();
@@ -643,35 +682,31 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
                 T V[3], t[3];
                 nested_terms<PL>(g, f.u0, f.u1, f.u2, c, V, t);
                 T (&w)[4][S::BY1][S::BX1] = s_xy[it % NW];
-                w[0][cy + R][cx + R] = nested_W<PL>(V[0], f.ei, f.u0, c);
-                w[1][cy + R][cx + R] = nested_G<PL>(t[0], f.ei, c);
-                w[2][cy + R][cx + R] = nested_W<PL>(V[1], f.ei, f.u1, c);
-                w[3][cy + R][cx + R] = nested_G<PL>(t[1], f.ei, c);
+                w[0][cy + R][cx + R] = nested_W<PL>(V[0], f, f.u0, c);
+                w[1][cy + R][cx + R] = nested_G<PL>(t[0], f, c);
+                w[2][cy + R][cx + R] = nested_W<PL>(V[1], f, f.u1, c);
+                w[3][cy + R][cx + R] = nested_G<PL>(t[1], f, c);
                 if (interior) {
                     const int sz = it % (2 * R + 1);
                     // read back only by this thread
-                    s_az[sz][0][cy][cx] = nested_W<PL>(V[2], f.ei, f.u2, c);
-                    s_az[sz][1][cy][cx] = nested_G<PL>(t[2], f.ei, c);
+                    s_az[sz][0][cy][cx] = nested_W<PL>(V[2], f, f.u2, c);
+                    s_az[sz][1][cy][cx] = nested_G<PL>(t[2], f, c);
                 }
             }
             constexpr int NST = (MODE == kModeRHS || MODE == kModeStage3) ? 5 : 10;
-            // The scheduler keeps to one neighbour pair at a time.  Left alone, in FP64 it
-            // requests every pair's LDS reads first, and the threads spill 27 to 92
-            // registers (their window takes about 130 of 256).
-            auto pair_fence = [] {
-                __builtin_amdgcn_sched_barrier(0x100);   // LDS reads may cross
-            };
             // 3. x and y sums at plane b = a (DB = 0) or a - 1 (DB = 1)
             auto sums_xy = [&](T (&to)[5]) {
                 const int pb = (it - DB) % NP, wb = (it - DB) % NW;
                 const int ly = cy + R, lx = cx + R;
-                const PF<T> s = centre_xy(Qb[slot(2 * R - DB)]);
-                auto ld = [&](int yy, int xx) {
+                const PF<T>& s = Qb[slot(2 * R - DB)];
+                const PF<T> sx = point_along<0>(s), sy = point_along<1>(s);
+                auto ld = [&](auto axis, int yy, int xx) {   // a neighbour along the axis
+                    constexpr int D = decltype(axis)::value;
                     PF<T> f;
                     f.rho = s_pl[pb][0][yy][xx];
                     f.E = s_pl[pb][1][yy][xx];
-                    f.ei = 0;
-                    if constexpr (PL) f.ei = s_pl[pb][kPlFields<T, PL> - 1][yy][xx];
+                    f.pk = 0;
+                    if constexpr (PL) f.pk = s_pl[pb][kPlFields<T, PL> - 1][yy][xx];
                     f.Th = s_pl[pb][2][yy][xx];
                     f.u0 = s_u[pb][0][yy + R][xx + R];
                     f.u1 = s_u[pb][1][yy + R][xx + R];
@@ -681,12 +716,13 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
                         f.m1 = s_pl[pb][4][yy][xx];
                         f.m2 = s_pl[pb][5][yy][xx];
                     } else {
-                        f.m0 = f.rho * f.u0;
-                        f.m1 = f.rho * f.u1;
-                        f.m2 = f.rho * f.u2;
+                        if constexpr (D == 0) f.m0 = s_mx[pb][yy - R][xx];
+                        else f.m1 = s_my[pb][yy][xx - R];
                     }
-                    return f;
+                    return point_along<D>(f);
                 };
+                constexpr std::integral_constant<int, 0> along_x{};
+                constexpr std::integral_constant<int, 1> along_y{};
                 T (&w)[4][S::BY1][S::BX1] = s_xy[wb];
                 ResidualSums<T, PL> rs;
                 rs.start(s, c);
@@ -694,18 +730,18 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
     #pragma unroll
                 for (int m = 1; m <= R; ++m) {
                     pair_fence();
-                    rs.template add<0>(s, ld(ly, lx + m), w[0][ly][lx + m], w[1][ly][lx + m], ld(ly, lx - m),
-                                       w[0][ly][lx - m], w[1][ly][lx - m], c, m - 1);
+                    rs.template add<0>(sx, ld(along_x, ly, lx + m), w[0][ly][lx + m], w[1][ly][lx + m],
+                                       ld(along_x, ly, lx - m), w[0][ly][lx - m], w[1][ly][lx - m], c, m - 1);
                 }
-                rs.template end<0>(s, c);
+                rs.template end<0>(sx, c);
                 rs.begin();
     #pragma unroll
                 for (int m = 1; m <= R; ++m) {
                     pair_fence();
-                    rs.template add<1>(s, ld(ly + m, lx), w[2][ly + m][lx], w[3][ly + m][lx], ld(ly - m, lx),
-                                       w[2][ly - m][lx], w[3][ly - m][lx], c, m - 1);
+                    rs.template add<1>(sy, ld(along_y, ly + m, lx), w[2][ly + m][lx], w[3][ly + m][lx],
+                                       ld(along_y, ly - m, lx), w[2][ly - m][lx], w[3][ly - m][lx], c, m - 1);
                 }
-                rs.template end<1>(s, c);
+                rs.template end<1>(sy, c);
                 rs.get(to);
             };
             const bool xy_here = it >= 3 * R + DB && it < zc + 3 * R + DB && interior;
@@ -733,7 +769,7 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
                         f.u0 = s_zt[k][5][cy][cx];
                         f.u1 = s_zt[k][6][cy][cx];
                         f.u2 = s_zt[k][7][cy][cx];
-                        f.ei = 0;
+                        f.pk = 0;
                         f.Th = s_zt[k][8][cy][cx];
                         return f;
                     } else {
@@ -859,6 +895,10 @@ struct SplitLds {
     using S = FusedShape<R, TX, TY>;
     T u[3][3][S::BY2][S::BX2];                    // three planes: a - 1, a and the next one
     T pl[3][kPlFields<T, PL>][S::BY1][S::BX1];
+    // FP64: rho u_0 of the tile's rows, rho u_1 of its columns (rows of even length: with
+    // these two 16 x 8 workgroups just fit a CU)
+    T mx[kMomentumInLds<T> ? 1 : 3][kMomentumInLds<T> ? 1 : TY][kMomentumInLds<T> ? 1 : TX + 2 * R];
+    T my[kMomentumInLds<T> ? 1 : 3][kMomentumInLds<T> ? 1 : TY + 2 * R][kMomentumInLds<T> ? 1 : TX];
     T xy[2][4][S::BY1][S::BX1];                   // (W_x, G_x, W_y, G_y) of planes a - 1, a
     T part[R][5][TY][TX];                         // partial residuals
 };
@@ -899,7 +939,7 @@ __device__ __forceinline__ void store_plane(LDS& lds, int bp, int yy, int xx, co
         lds.pl[bp][4][yy + R][xx + R] = f.m1;
         lds.pl[bp][5][yy + R][xx + R] = f.m2;
     }
-    if constexpr (PL) lds.pl[bp][kPlFields<T, PL> - 1][yy + R][xx + R] = f.ei;
+    if constexpr (PL) lds.pl[bp][kPlFields<T, PL> - 1][yy + R][xx + R] = f.pk;
 }
 
 // Runs body(phase, it) for it = 0 .. iters - 1, phase = it % W a constant: register slots
@@ -968,7 +1008,13 @@ __device__ __forceinline__ void split_columns(SplitLds<T, R, TX, TY, PL>& lds, c
         __builtin_amdgcn_sched_barrier(0);
         Qb[slot(3 * R)] = make_pf<T, kPlain<T, MODE>>(cq0, cq1, cq2, cq3, cq4, c);
         const bool do_grad = it >= 2 * R, do_out = it >= 4 * R;
-        if (do_grad) store_plane<T, R, PL>(lds, bp, cy, cx, Qb[slot(2 * R)]);
+        if (do_grad) {
+            store_plane<T, R, PL>(lds, bp, cy, cx, Qb[slot(2 * R)]);
+            if constexpr (!kMomentumInLds<T>) {
+                lds.mx[bp][cy][cx + R] = Qb[slot(2 * R)].m0;
+                lds.my[bp][cy + R][cx] = Qb[slot(2 * R)].m1;
+            }
+        }
         __syncthreads();
         if (do_grad) {
             T g[3][3], V[3], t[3];
@@ -977,12 +1023,12 @@ __device__ __forceinline__ void split_columns(SplitLds<T, R, TX, TY, PL>& lds, c
             const PF<T>& f = Qb[slot(2 * R)];
             nested_terms<PL>(g, f.u0, f.u1, f.u2, c, V, t);
             auto& w = lds.xy[it & 1];
-            w[0][cy + R][cx + R] = nested_W<PL>(V[0], f.ei, f.u0, c);
-            w[1][cy + R][cx + R] = nested_G<PL>(t[0], f.ei, c);
-            w[2][cy + R][cx + R] = nested_W<PL>(V[1], f.ei, f.u1, c);
-            w[3][cy + R][cx + R] = nested_G<PL>(t[1], f.ei, c);
-            Wz[slot(2 * R)] = nested_W<PL>(V[2], f.ei, f.u2, c);
-            Gz[slot(2 * R)] = nested_G<PL>(t[2], f.ei, c);
+            w[0][cy + R][cx + R] = nested_W<PL>(V[0], f, f.u0, c);
+            w[1][cy + R][cx + R] = nested_G<PL>(t[0], f, c);
+            w[2][cy + R][cx + R] = nested_W<PL>(V[1], f, f.u1, c);
+            w[3][cy + R][cx + R] = nested_G<PL>(t[1], f, c);
+            Wz[slot(2 * R)] = nested_W<PL>(V[2], f, f.u2, c);
+            Gz[slot(2 * R)] = nested_G<PL>(t[2], f, c);
         }
         T dn[5], qn[5];
         if (do_out) {
@@ -1114,13 +1160,19 @@ __device__ __forceinline__ void split_planes(SplitLds<T, R, TX, TY, PL>& lds, co
         const bool do_grad = it >= 2 * R;
         if (has_col) {
             Hb[slot(3 * R)] = make_pf<T, kPlain<T, MODE>>(cq0, cq1, cq2, cq3, cq4, c);
-            if (do_grad) store_plane<T, R, PL>(lds, bp, hy, hx, Hb[slot(2 * R)]);
+            // FP64: the window holds one momentum component, along the ring column's axis
+            if constexpr (!kMomentumInLds<T>) Hb[slot(3 * R)].m0 = t < S::NHX ? cq1 : cq2;
+            if (do_grad) {
+                store_plane<T, R, PL>(lds, bp, hy, hx, Hb[slot(2 * R)]);
+                if constexpr (!kMomentumInLds<T>)
+                    *(t < S::NHX ? &lds.mx[bp][hy][hx + R] : &lds.my[bp][hy + R][hx]) = Hb[slot(2 * R)].m0;
+            }
         }
         if (do_grad && has_out) {
             const T rr = fast_recip(cr0);
-            lds.u[bp][0][oy + 2 * R][ox + 2 * R] = cr1 * rr;
-            lds.u[bp][1][oy + 2 * R][ox + 2 * R] = cr2 * rr;
-            lds.u[bp][2][oy + 2 * R][ox + 2 * R] = cr3 * rr;
+            lds.u[bp][0][oy + 2 * R][ox + 2 * R] = velocity<PL>(cr1, cr0, rr);
+            lds.u[bp][1][oy + 2 * R][ox + 2 * R] = velocity<PL>(cr2, cr0, rr);
+            lds.u[bp][2][oy + 2 * R][ox + 2 * R] = velocity<PL>(cr3, cr0, rr);
         }
         __syncthreads();
         if (do_grad && has_col) {
@@ -1130,22 +1182,23 @@ __device__ __forceinline__ void split_planes(SplitLds<T, R, TX, TY, PL>& lds, co
             const PF<T>& f = Hb[slot(2 * R)];
             nested_terms<PL>(g, f.u0, f.u1, f.u2, c, V, tt);
             auto& w = lds.xy[it & 1];
-            w[0][hy + R][hx + R] = nested_W<PL>(V[0], f.ei, f.u0, c);
-            w[1][hy + R][hx + R] = nested_G<PL>(tt[0], f.ei, c);
-            w[2][hy + R][hx + R] = nested_W<PL>(V[1], f.ei, f.u1, c);
-            w[3][hy + R][hx + R] = nested_G<PL>(tt[1], f.ei, c);
+            w[0][hy + R][hx + R] = nested_W<PL>(V[0], f, f.u0, c);
+            w[1][hy + R][hx + R] = nested_G<PL>(tt[0], f, c);
+            w[2][hy + R][hx + R] = nested_W<PL>(V[1], f, f.u1, c);
+            w[3][hy + R][hx + R] = nested_G<PL>(tt[1], f, c);
         }
         // x and y sums of plane a - 1
         if (it >= 3 * R + 1 && it < zc + 3 * R + 1) {
             const int pb = (it - 1) % 3;
             const auto& w = lds.xy[(it - 1) & 1];
             const int ly = cy + R, lx = cx + R;
-            auto ld = [&](int yy, int xx) {
+            auto ld = [&](auto axis, int yy, int xx) {   // a point of the sums along the axis
+                constexpr int D = decltype(axis)::value;
                 PF<T> f;
                 f.rho = lds.pl[pb][0][yy][xx];
                 f.E = lds.pl[pb][1][yy][xx];
-                f.ei = 0;
-                if constexpr (PL) f.ei = lds.pl[pb][kPlFields<T, PL> - 1][yy][xx];
+                f.pk = 0;
+                if constexpr (PL) f.pk = lds.pl[pb][kPlFields<T, PL> - 1][yy][xx];
                 f.Th = lds.pl[pb][2][yy][xx];
                 f.u0 = lds.u[pb][0][yy + R][xx + R];
                 f.u1 = lds.u[pb][1][yy + R][xx + R];
@@ -1154,26 +1207,34 @@ __device__ __forceinline__ void split_planes(SplitLds<T, R, TX, TY, PL>& lds, co
                     f.m0 = lds.pl[pb][3][yy][xx];
                     f.m1 = lds.pl[pb][4][yy][xx];
                     f.m2 = lds.pl[pb][5][yy][xx];
-                    return f;
                 } else {
-                    return centre_xy(f);
+                    if constexpr (D == 0) f.m0 = lds.mx[pb][yy - R][xx];
+                    else f.m1 = lds.my[pb][yy][xx - R];
                 }
+                return point_along<D>(f);
             };
-            const PF<T> s = ld(ly, lx);
+            constexpr std::integral_constant<int, 0> along_x{};
+            constexpr std::integral_constant<int, 1> along_y{};
+            const PF<T> sx = ld(along_x, ly, lx);
             ResidualSums<T, PL> rs;
-            rs.start(s, c);
+            rs.start(sx, c);
             rs.begin();
 #pragma unroll
-            for (int m = 1; m <= R; ++m)
-                rs.template add<0>(s, ld(ly, lx + m), w[0][ly][lx + m], w[1][ly][lx + m], ld(ly, lx - m),
-                                   w[0][ly][lx - m], w[1][ly][lx - m], c, m - 1);
-            rs.template end<0>(s, c);
+            for (int m = 1; m <= R; ++m) {
+                pair_fence();
+                rs.template add<0>(sx, ld(along_x, ly, lx + m), w[0][ly][lx + m], w[1][ly][lx + m],
+                                   ld(along_x, ly, lx - m), w[0][ly][lx - m], w[1][ly][lx - m], c, m - 1);
+            }
+            rs.template end<0>(sx, c);
+            const PF<T> sy = ld(along_y, ly, lx);
             rs.begin();
 #pragma unroll
-            for (int m = 1; m <= R; ++m)
-                rs.template add<1>(s, ld(ly + m, lx), w[2][ly + m][lx], w[3][ly + m][lx], ld(ly - m, lx),
-                                   w[2][ly - m][lx], w[3][ly - m][lx], c, m - 1);
-            rs.template end<1>(s, c);
+            for (int m = 1; m <= R; ++m) {
+                pair_fence();
+                rs.template add<1>(sy, ld(along_y, ly + m, lx), w[2][ly + m][lx], w[3][ly + m][lx],
+                                   ld(along_y, ly - m, lx), w[2][ly - m][lx], w[3][ly - m][lx], c, m - 1);
+            }
+            rs.template end<1>(sy, c);
             auto& pp = lds.part[it % R];
             T sums[5];
             rs.get(sums);

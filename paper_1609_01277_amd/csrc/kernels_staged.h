@@ -49,9 +49,10 @@ constexpr int kStagedTile = 16;
 // run_planes).  Runs of 32 and 128 measure the same at 512^3, orders 8 and 12.
 constexpr int kNestedRun = 64;
 // Fields of a strip: rho, rho E, Th, u_i, then W_d, G_d of the strip's axis d (see
-// nested_terms), then the momentum where LDS keeps it (kMomentumInLds).
+// nested_terms), then the momentum where LDS keeps it (kMomentumInLds), its component along
+// the axis elsewhere.
 template <typename T, bool PL>
-constexpr int kStagedFields = (kMomentumInLds<T> ? 11 : 8) + (PL ? 1 : 0);   // and p where W, G have none of it
+constexpr int kStagedFields = (kMomentumInLds<T> ? 11 : 9) + (PL ? 1 : 0);   // and p where W, G have none of it
 
 // The unit of work of a tiled launch is (tile, run of zc planes).  Units are
 // numbered by pairs of x-adjacent tiles, plane run by plane run within a pair
@@ -110,12 +111,13 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
     auto point_at = [&](int64_t ix) {
         return make_pf<T, PL>(q[ix], q[P + ix], q[2 * P + ix], q[3 * P + ix], q[4 * P + ix], c);
     };
-    auto lds_point = [&](int i) {
+    auto lds_point = [&](auto axis, int i) {
+        constexpr int D = decltype(axis)::value;
         PF<T> p;
         p.rho = sb[0][i];
         p.E = sb[1][i];
-        p.ei = 0;
-        if constexpr (PL) p.ei = sb[kStagedFields<T, PL> - 1][i];
+        p.pk = 0;
+        if constexpr (PL) p.pk = sb[kStagedFields<T, PL> - 1][i];
         p.Th = sb[2][i];
         p.u0 = sb[3][i];
         p.u1 = sb[4][i];
@@ -125,14 +127,14 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             p.m1 = sb[9][i];
             p.m2 = sb[10][i];
         } else {
-            p.m0 = p.rho * p.u0;
-            p.m1 = p.rho * p.u1;
-            p.m2 = p.rho * p.u2;
+            (D == 0 ? p.m0 : p.m1) = sb[8][i];
         }
-        return p;
+        return point_along<D>(p);
     };
+    constexpr std::integral_constant<int, 0> along_x{};
+    constexpr std::integral_constant<int, 1> along_y{};
     // a point mirrored across x (fx) and/or y (fy), and the nested pair of the strip
-    auto put = [&](int i, const PF<T>& p, unsigned fx, unsigned fy, T W, T G) {
+    auto put = [&](auto axis, int i, const PF<T>& p, unsigned fx, unsigned fy, T W, T G) {
         sb[0][i] = p.rho;
         sb[1][i] = p.E;
         sb[2][i] = p.Th;
@@ -145,19 +147,21 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             sb[8][i] = flip_sign(p.m0, fx);
             sb[9][i] = flip_sign(p.m1, fy);
             sb[10][i] = p.m2;
+        } else {
+            sb[8][i] = decltype(axis)::value == 0 ? flip_sign(p.m0, fx) : flip_sign(p.m1, fy);
         }
-        if constexpr (PL) sb[kStagedFields<T, PL> - 1][i] = p.ei;
+        if constexpr (PL) sb[kStagedFields<T, PL> - 1][i] = p.pk;
     };
     for (int z = z0; z < z1; ++z) {
         const int64_t pz = (int64_t)z * plane, id = pz + col;
         const PF<T> s = point_at(id);
-        auto W_of = [&](T V, const PF<T>& p, T u) { return nested_W<PL>(V, p.ei, u, c); };
-        auto G_of = [&](T t, const PF<T>& p) { return nested_G<PL>(t, p.ei, c); };
-        const PF<T> sxy = centre_xy(s);
+        auto W_of = [&](T V, const PF<T>& p, T u) { return nested_W<PL>(V, p, u, c); };
+        auto G_of = [&](T t, const PF<T>& p) { return nested_G<PL>(t, p, c); };
+        const PF<T> sx = point_along<0>(s), sy = point_along<1>(s);
         ResidualSums<T, PL> rs;
         rs.start(s, c);
         __syncthreads();   // the previous plane's y-strip reads are done
-        put(cy * SW + R + cx, s, fxo, fyo, flip_sign(W_of(nf[id], s, s.u0), fxo), G_of(nf[3 * P + id], s));   // W_x: odd under an x mirror
+        put(along_x, cy * SW + R + cx, s, fxo, fyo, flip_sign(W_of(nf[id], s, s.u0), fxo), G_of(nf[3 * P + id], s));   // W_x: odd under an x mirror
         for (int e = tid; e < NA; e += NT) {
             const int side = e / (R * TS), r = e % (R * TS);
             const int ly = r / R, lx = side ? R + TS + r % R : r % R;
@@ -165,7 +169,7 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             const int64_t ix = pz + (int64_t)fold_index(y0 + ly, ny, c.sym[1], fy) * nx +
                                fold_index(x0 - R + lx, nx, c.sym[0], fx);
             const PF<T> p = point_at(ix);
-            put(ly * SW + lx, p, fx, fy, flip_sign(W_of(nf[ix], p, p.u0), fx), G_of(nf[3 * P + ix], p));
+            put(along_x, ly * SW + lx, p, fx, fy, flip_sign(W_of(nf[ix], p, p.u0), fx), G_of(nf[3 * P + ix], p));
         }
         __syncthreads();
         {
@@ -173,12 +177,12 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             rs.begin();
 #pragma unroll 1
             for (int m = 1; m <= R; ++m)
-                rs.template add<0>(sxy, lds_point(i + m), sb[6][i + m], sb[7][i + m], lds_point(i - m), sb[6][i - m],
-                                   sb[7][i - m], c, m - 1);
-            rs.template end<0>(sxy, c);
+                rs.template add<0>(sx, lds_point(along_x, i + m), sb[6][i + m], sb[7][i + m], lds_point(along_x, i - m),
+                                   sb[6][i - m], sb[7][i - m], c, m - 1);
+            rs.template end<0>(sx, c);
         }
         __syncthreads();   // the x-strip reads are done
-        put((R + cy) * TS + cx, s, fxo, fyo, flip_sign(W_of(nf[P + id], s, s.u1), fyo), G_of(nf[4 * P + id], s));   // W_y: odd under a y mirror
+        put(along_y, (R + cy) * TS + cx, s, fxo, fyo, flip_sign(W_of(nf[P + id], s, s.u1), fyo), G_of(nf[4 * P + id], s));   // W_y: odd under a y mirror
         for (int e = tid; e < NA; e += NT) {
             const int side = e / (R * TS), r = e % (R * TS);
             const int lx = r % TS, ly = side ? R + TS + r / TS : r / TS;
@@ -186,7 +190,7 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             const int64_t ix = pz + (int64_t)fold_index(y0 - R + ly, ny, c.sym[1], fy) * nx +
                                fold_index(x0 + lx, nx, c.sym[0], fx);
             const PF<T> p = point_at(ix);
-            put(ly * TS + lx, p, fx, fy, flip_sign(W_of(nf[P + ix], p, p.u1), fy), G_of(nf[4 * P + ix], p));
+            put(along_y, ly * TS + lx, p, fx, fy, flip_sign(W_of(nf[P + ix], p, p.u1), fy), G_of(nf[4 * P + ix], p));
         }
         __syncthreads();
         {
@@ -194,9 +198,9 @@ __global__ void __launch_bounds__(kStagedTile * kStagedTile)
             rs.begin();
 #pragma unroll 1
             for (int m = 1; m <= R; ++m)
-                rs.template add<1>(sxy, lds_point(i + m * TS), sb[6][i + m * TS], sb[7][i + m * TS], lds_point(i - m * TS),
-                                   sb[6][i - m * TS], sb[7][i - m * TS], c, m - 1);
-            rs.template end<1>(sxy, c);
+                rs.template add<1>(sy, lds_point(along_y, i + m * TS), sb[6][i + m * TS], sb[7][i + m * TS],
+                                   lds_point(along_y, i - m * TS), sb[6][i - m * TS], sb[7][i - m * TS], c, m - 1);
+            rs.template end<1>(sy, c);
         }
         {
             const PF<T> sz = z_point<T, R>(s);
@@ -301,10 +305,10 @@ __global__ void __launch_bounds__(TS * TS)
     auto own_u = [&](int z, T (&u)[3]) {
         unsigned fz;
         const int64_t id = (int64_t)map_index(z, nz, c.sym[2], fz) * plane + col;
-        const T rr = fast_recip(q[id]);
-        u[0] = q[P + id] * rr;
-        u[1] = q[2 * P + id] * rr;
-        u[2] = flip_sign(q[3 * P + id] * rr, fz);
+        const T rho = q[id], rr = fast_recip(rho);
+        u[0] = velocity<PL>(q[P + id], rho, rr);
+        u[1] = velocity<PL>(q[2 * P + id], rho, rr);
+        u[2] = flip_sign(velocity<PL>(q[3 * P + id], rho, rr), fz);
     };
     T ring[W][3];
 #pragma unroll
@@ -342,18 +346,18 @@ __global__ void __launch_bounds__(TS * TS)
             unsigned fz;
             map_index(z + R, nz, c.sym[2], fz);
             const T rr = fast_recip(pe[0]);
-            ring[slot(2 * R)][0] = pe[1] * rr;
-            ring[slot(2 * R)][1] = pe[2] * rr;
-            ring[slot(2 * R)][2] = flip_sign(pe[3] * rr, fz);
+            ring[slot(2 * R)][0] = velocity<PL>(pe[1], pe[0], rr);
+            ring[slot(2 * R)][1] = velocity<PL>(pe[2], pe[0], rr);
+            ring[slot(2 * R)][2] = flip_sign(velocity<PL>(pe[3], pe[0], rr), fz);
         }
 #pragma unroll
         for (int k = 0; k < APT; ++k) {
             if (aoff[k] >= 0) {
                 const T rr = fast_recip(pa[k][0]);
                 T* s0 = &su[b][0][0][0];
-                s0[aoff[k]] = flip_sign(pa[k][1] * rr, afx[k]);
-                s0[BW * BW + aoff[k]] = flip_sign(pa[k][2] * rr, afy[k]);
-                s0[2 * BW * BW + aoff[k]] = pa[k][3] * rr;
+                s0[aoff[k]] = flip_sign(velocity<PL>(pa[k][1], pa[k][0], rr), afx[k]);
+                s0[BW * BW + aoff[k]] = flip_sign(velocity<PL>(pa[k][2], pa[k][0], rr), afy[k]);
+                s0[2 * BW * BW + aoff[k]] = velocity<PL>(pa[k][3], pa[k][0], rr);
             }
         }
         const T (&uc)[3] = ring[slot(R)];

@@ -16,6 +16,9 @@
 // its window (spills: 1,943 -> 2,221 us at order 12): there W_z, G_z and Th of the window
 // are in LDS, which pays for it with single buffers and a second barrier a plane (A: the
 // plane is staged, B: its sums are done), the columns passing A amid their z sums.
+// There rho u_2 of the window is not held either but formed as rho u_2 + r from its remainder
+// r = m - rho u_2, which is at most a rounding of m and needs no more than FP32: r's own
+// rounding is 2^-24 of a unit in m's last place, so the sum rounds to m itself.
 // The residual step at 256^3, FP64, order 8: 1,231 -> 880 us, 3.3 GB at 3.75 TB/s (a copy
 // reaches 4.6), VALU 40 %, LDS 34 %; order 12: 1,619 -> 1,150.
 #pragma once
@@ -24,14 +27,21 @@
 
 namespace sbli {
 
-// Fields of a staged plane: rho, rho E, Th, u_i, (W_x, G_x), (W_y, G_y), then the momentum
-// where LDS keeps it, then p where the plain formulation needs it.
+// Fields of a staged plane over the tile and its arms: rho, rho E, Th, u_i, then the
+// momentum where LDS keeps it, then p where the plain formulation needs it; and over the
+// tile and the arms of one axis: W and G of that axis and the momentum along it (FP64).
 template <typename T, bool PL>
-constexpr int kMarchFields = (kMomentumInLds<T> ? 13 : 10) + (PL ? 1 : 0);
+constexpr int kMarchFields = (kMomentumInLds<T> ? 9 : 6) + (PL ? 1 : 0);
+template <typename T>
+constexpr int kMarchAxisFields = kMomentumInLds<T> ? 2 : 3;
 
 // FP64 at orders 10 and 12: (W_z, G_z, Th) of the window in LDS, single buffers.
 template <typename T, int R>
 constexpr bool kMarchZLds = sizeof(T) == 8 && R >= 5;
+
+// FP64 at orders 10 and 12: rho u_2 of the window from its remainder.
+template <typename T, int R>
+constexpr bool kMarchRem = sizeof(T) == 8 && R >= 5;
 
 template <typename T, int R, bool PL>
 struct MarchLds {
@@ -39,8 +49,11 @@ struct MarchLds {
     // zr first: an LDS instruction's offset reaches 64 KB
     static constexpr int ZS = kMarchZLds<T, R> ? TS : 1;
     T zr[kMarchZLds<T, R> ? 2 * R + 1 : 1][3][ZS][ZS];
+    static constexpr int RS = kMarchRem<T, R> ? TS : 1;
+    float rem[kMarchRem<T, R> ? 2 * R + 1 : 1][RS][RS];
     T part[NB][5][TS][TS];
     T f[NB][kMarchFields<T, PL>][SW][SW];
+    T w[NB][2][kMarchAxisFields<T>][TS * SW];   // x axis: rows of SW points; y axis: of TS
 };
 
 template <typename T, int R, int MODE>
@@ -79,7 +92,8 @@ __device__ __forceinline__ void march_columns(MarchLds<T, R, kPlain<T, MODE>>& l
     auto enter = [&](int k) {                      // the requested plane, converted
         PF<T>& s = win[k];
         s = make_pf<T, PL>(p0, p1, p2, flip_sign(p3, pf), p4, c);
-        const T w = nested_W<PL>(flip_sign(pv, pf), s.ei, s.u2, c), g = nested_G<PL>(pt, s.ei, c);
+        const T w = nested_W<PL>(flip_sign(pv, pf), s, s.u2, c), g = nested_G<PL>(pt, s, c);
+        if constexpr (kMarchRem<T, R>) lds.rem[k][cy][cx] = (float)fmaT(-s.rho, s.u2, s.m2);
         if constexpr (ZL) {
             lds.zr[k][0][cy][cx] = w;
             lds.zr[k][1][cy][cx] = g;
@@ -94,10 +108,11 @@ __device__ __forceinline__ void march_columns(MarchLds<T, R, kPlain<T, MODE>>& l
     auto plane_of = [&](int k) {                   // point of the window for the z sums
         PF<T> s = win[k];
         if constexpr (ZL) s.Th = lds.zr[k][2][cy][cx];
+        if constexpr (kMarchRem<T, R>) s.m2 = fmaT(s.rho, s.u2, (T)lds.rem[k][cy][cx]);
         return z_point<T, R>(with_pressure<PL>(s, c));
     };
-    T pd[5] = {0, 0, 0, 0, 0}, pm[3] = {0, 0, 0};
-    auto issue_own = [&](int z) {                  // dq and the momentum of an output plane
+    T pd[5] = {0, 0, 0, 0, 0}, pm[2] = {0, 0};
+    auto issue_own = [&](int z) {                  // dq, rho u_0 and rho u_1 of an output plane
         const int64_t i = (int64_t)z * plane + dcol;
         if constexpr (DQ) {
 #pragma unroll
@@ -105,7 +120,7 @@ __device__ __forceinline__ void march_columns(MarchLds<T, R, kPlain<T, MODE>>& l
         }
         if constexpr (ZU && MODE != kModeRHS) {
 #pragma unroll
-            for (int f = 0; f < 3; ++f) pm[f] = q[(1 + f) * P + i];
+            for (int f = 0; f < 2; ++f) pm[f] = q[(1 + f) * P + i];
         }
     };
     issue(z0 - R);
@@ -145,7 +160,7 @@ __device__ __forceinline__ void march_columns(MarchLds<T, R, kPlain<T, MODE>>& l
             for (int f = 0; f < 5; ++f) Rv[f] += clos[f * P + id];
         }
         const PF<T>& w0 = win[slot(R)];
-        const T qv[5] = {w0.rho, ZU ? pm[0] : w0.m0, ZU ? pm[1] : w0.m1, ZU ? pm[2] : w0.m2, w0.E};
+        const T qv[5] = {w0.rho, ZU ? pm[0] : w0.m0, ZU ? pm[1] : w0.m1, ZU ? s.m2 : w0.m2, w0.E};
         T dn[5], qn[5];
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
@@ -181,6 +196,7 @@ __device__ __forceinline__ void march_planes(MarchLds<T, R, kPlain<T, MODE>>& ld
                                              int run) {
     constexpr int TS = kStagedTile, NT = TS * TS;
     constexpr int NB = MarchLds<T, R, kPlain<T, MODE>>::NB;
+    constexpr int SW = TS + 2 * R;
     constexpr int NARM = 4 * R * TS, APT = (NARM + NT - 1) / NT;
     constexpr bool PL = kPlain<T, MODE>;
     const int nx = c.n[0], ny = c.n[1];
@@ -242,11 +258,19 @@ __device__ __forceinline__ void march_planes(MarchLds<T, R, kPlain<T, MODE>>& ld
         f[4][y][x] = flip_sign(p.u1, fy);
         f[5][y][x] = p.u2;
         if constexpr (kMomentumInLds<T>) {
-            f[10][y][x] = flip_sign(p.m0, fx);
-            f[11][y][x] = flip_sign(p.m1, fy);
-            f[12][y][x] = p.m2;
+            f[6][y][x] = flip_sign(p.m0, fx);
+            f[7][y][x] = flip_sign(p.m1, fy);
+            f[8][y][x] = p.m2;
         }
-        if constexpr (PL) f[kMarchFields<T, PL> - 1][y][x] = p.ei;
+        if constexpr (PL) f[kMarchFields<T, PL> - 1][y][x] = p.pk;
+    };
+    // the fields of one axis (0: x, 1: y) at element i of their rows
+    auto put_axis = [&](int b, int axis, int i, const PF<T>& p, T V, T t, unsigned fx, unsigned fy) {
+        T* w = &lds.w[b][axis][0][i];
+        // W is odd under a mirror of its axis, and so is the momentum along it
+        w[0] = flip_sign(nested_W<PL>(V, p, axis ? p.u1 : p.u0, c), axis ? fy : fx);
+        w[TS * SW] = nested_G<PL>(t, p, c);
+        if constexpr (!kMomentumInLds<T>) w[2 * TS * SW] = axis ? flip_sign(p.m1, fy) : flip_sign(p.m0, fx);
     };
     issue(z0);
     for (int it = 0; it < run; ++it) {
@@ -254,24 +278,24 @@ __device__ __forceinline__ void march_planes(MarchLds<T, R, kPlain<T, MODE>>& ld
         auto& f = lds.f[b];
         const PF<T> s0 = make_pf<T, PL>(po[0], po[1], po[2], po[3], po[4], c);
         put(b, R + cy, R + cx, s0, fxo, fyo);
-        f[6][R + cy][R + cx] = flip_sign(nested_W<PL>(po[5], s0.ei, s0.u0, c), fxo);   // W_x: odd under an x mirror
-        f[7][R + cy][R + cx] = nested_G<PL>(po[6], s0.ei, c);
-        f[8][R + cy][R + cx] = flip_sign(nested_W<PL>(po[7], s0.ei, s0.u1, c), fyo);
-        f[9][R + cy][R + cx] = nested_G<PL>(po[8], s0.ei, c);
+        put_axis(b, 0, cy * SW + R + cx, s0, po[5], po[6], fxo, fyo);
+        put_axis(b, 1, (R + cy) * TS + cx, s0, po[7], po[8], fxo, fyo);
 #pragma unroll
         for (int k = 0; k < APT; ++k) {
             if (ax[k] >= 0) {
                 const PF<T> p = make_pf<T, PL>(pa[k][0], pa[k][1], pa[k][2], pa[k][3], pa[k][4], c);
                 put(b, ay[k], ax[k], p, afx[k], afy[k]);
-                f[6 + 2 * pair[k]][ay[k]][ax[k]] =
-                    flip_sign(nested_W<PL>(pa[k][5], p.ei, pair[k] ? p.u1 : p.u0, c), pair[k] ? afy[k] : afx[k]);
-                f[7 + 2 * pair[k]][ay[k]][ax[k]] = nested_G<PL>(pa[k][6], p.ei, c);
+                put_axis(b, pair[k], pair[k] ? ay[k] * TS + ax[k] - R : (ay[k] - R) * SW + ax[k], p, pa[k][5], pa[k][6],
+                         afx[k], afy[k]);
             }
         }
         if (it + 1 < run) issue(z0 + it + 1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        auto ld = [&](int y, int x) {
+        const auto& wx = lds.w[b][0];
+        const auto& wy = lds.w[b][1];
+        auto ld = [&](auto axis, int y, int x) {
+            constexpr int D = decltype(axis)::value;
             PF<T> p;
             p.rho = f[0][y][x];
             p.E = f[1][y][x];
@@ -279,33 +303,46 @@ __device__ __forceinline__ void march_planes(MarchLds<T, R, kPlain<T, MODE>>& ld
             p.u0 = f[3][y][x];
             p.u1 = f[4][y][x];
             p.u2 = f[5][y][x];
-            p.ei = 0;
-            if constexpr (PL) p.ei = f[kMarchFields<T, PL> - 1][y][x];
+            p.pk = 0;
+            if constexpr (PL) p.pk = f[kMarchFields<T, PL> - 1][y][x];
             if constexpr (kMomentumInLds<T>) {
-                p.m0 = f[10][y][x];
-                p.m1 = f[11][y][x];
-                p.m2 = f[12][y][x];
-                return p;
+                p.m0 = f[6][y][x];
+                p.m1 = f[7][y][x];
+                p.m2 = f[8][y][x];
+            } else if constexpr (D == 0) {
+                p.m0 = wx[2][(y - R) * SW + x];
             } else {
-                return centre_xy(p);
+                p.m1 = wy[2][y * TS + x - R];
             }
+            return point_along<D>(p);
         };
+        constexpr std::integral_constant<int, 0> along_x{};
+        constexpr std::integral_constant<int, 1> along_y{};
         const int ly = cy + R, lx = cx + R;
-        const PF<T> s = centre_xy(s0);
+        const int ix = cy * SW + lx, iy = ly * TS + cx;
+        auto one_pair = [] {   // at orders 10 and 12 the threads spill without (7 to 22 registers)
+            if constexpr (sizeof(T) == 8 && R >= 5) pair_fence();
+        };
+        const PF<T> sx = point_along<0>(s0);
         ResidualSums<T, PL> rs;
-        rs.start(s, c);
+        rs.start(s0, c);
         rs.begin();
 #pragma unroll
-        for (int m = 1; m <= R; ++m)
-            rs.template add<0>(s, ld(ly, lx + m), f[6][ly][lx + m], f[7][ly][lx + m], ld(ly, lx - m), f[6][ly][lx - m],
-                               f[7][ly][lx - m], c, m - 1);
-        rs.template end<0>(s, c);
+        for (int m = 1; m <= R; ++m) {
+            one_pair();
+            rs.template add<0>(sx, ld(along_x, ly, lx + m), wx[0][ix + m], wx[1][ix + m], ld(along_x, ly, lx - m),
+                               wx[0][ix - m], wx[1][ix - m], c, m - 1);
+        }
+        rs.template end<0>(sx, c);
+        const PF<T> sy = point_along<1>(s0);
         rs.begin();
 #pragma unroll
-        for (int m = 1; m <= R; ++m)
-            rs.template add<1>(s, ld(ly + m, lx), f[8][ly + m][lx], f[9][ly + m][lx], ld(ly - m, lx), f[8][ly - m][lx],
-                               f[9][ly - m][lx], c, m - 1);
-        rs.template end<1>(s, c);
+        for (int m = 1; m <= R; ++m) {
+            one_pair();
+            rs.template add<1>(sy, ld(along_y, ly + m, lx), wy[0][iy + m * TS], wy[1][iy + m * TS],
+                               ld(along_y, ly - m, lx), wy[0][iy - m * TS], wy[1][iy - m * TS], c, m - 1);
+        }
+        rs.template end<1>(sy, c);
         T sums[5];
         rs.get(sums);
 #pragma unroll
