@@ -152,6 +152,12 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  * for orders 6 (FP32: up to 96^3 points) and 8 while its scratch is at most 1/64 of the
  * device's free memory, else a fused variant and a zchunk that fill the device.
  *
+ * Graphs: sbli_rhs and sbli_rk3_step may be captured (the context's stream capturing).  The
+ * staged form's scratch belongs to the context, so what is recorded with it must not run
+ * beside other work of the context, another such graph included.  Where the staged form is
+ * only sbli_init's choice, a captured call records the fused form instead, which has no
+ * such state; sbli_set_tuning, sbli_autotune and orders 10 and 12 make it the caller's.
+ *
  * sbli_num_variants: number of variants for the context (>= 1), or < 0 on error.
  * sbli_variant_info: info = {tile x, tile y, load-ahead depth, register-window
  *   rotation (1) or shifting (0), wavefronts per SIMD its register allocation

@@ -31,6 +31,8 @@ struct sbli_ctx {
     BoxConst<float> c32;
     int zchunk;             // z-planes per workgroup of the fused stage kernel
     int variant;            // index into the compiled stage variants of (dtype, order)
+    bool by_rule;           // the staged form is sbli_init's choice, not the caller's:
+    int graph_variant, graph_zchunk;   // graphs then record this fused configuration
     BoxInst<double> inst64; // launch table entry (host copy) of the box
     BoxInst<float> inst32;
     void* inst_dev;         // the same entry on the device
@@ -226,20 +228,25 @@ static bool prefers_staged(const sbli_params* p, int r) {
     return scratch <= free_b / 64.0;
 }
 
-// Rebuilds the box's launch-table entry for the current variant and zchunk and
-// copies it to the device, ordered on the context's stream, then waits for the
-// copy so the host copy may change again.  The step time is 1 in the table;
-// each launch passes the actual dt as its scale.
+// Rebuilds the box's launch-table entry for the fused configuration in use (the current
+// one, or the one that graphs record) and copies it to the device, ordered on the context's
+// stream, then waits for the copy so the host copy may change again.  The step time is 1 in
+// the table; each launch passes the actual dt as its scale.
 static hipError_t update_table(sbli_ctx* x) {
-    if (is_staged(x, x->variant)) return ensure_staged_scratch(x);   // no launch table
-    const StageVariant v = variant_of(x, x->variant);
+    const bool staged = is_staged(x, x->variant);
+    if (staged) {
+        const hipError_t e = ensure_staged_scratch(x);
+        if (e != hipSuccess || !x->by_rule) return e;
+    }
+    const StageVariant v = variant_of(x, staged ? x->graph_variant : x->variant);
+    const int zchunk = staged ? x->graph_zchunk : x->zchunk;
     if (x->p.dtype == SBLI_F64) {
         x->inst64.c = x->c64;
         x->inst64.offset = 0;
         x->inst64.dt = 1.0;
         x->inst64.closure = nullptr;
         x->inst64.cflag = nullptr;
-        set_box_geometry(x->inst64, v.tx, v.ty, x->zchunk, 0);
+        set_box_geometry(x->inst64, v.tx, v.ty, zchunk, 0);
         hipError_t e = hipMemcpyAsync(x->inst_dev, &x->inst64, sizeof(x->inst64), hipMemcpyHostToDevice, x->stream);
         return e == hipSuccess ? hipStreamSynchronize(x->stream) : e;
     }
@@ -248,7 +255,7 @@ static hipError_t update_table(sbli_ctx* x) {
     x->inst32.dt = 1.0f;
     x->inst32.closure = x->net ? x->clos : nullptr;
     x->inst32.cflag = x->net ? x->cflag : nullptr;
-    set_box_geometry(x->inst32, v.tx, v.ty, x->zchunk, 0);
+    set_box_geometry(x->inst32, v.tx, v.ty, zchunk, 0);
     hipError_t e = hipMemcpyAsync(x->inst_dev, &x->inst32, sizeof(x->inst32), hipMemcpyHostToDevice, x->stream);
     return e == hipSuccess ? hipStreamSynchronize(x->stream) : e;
 }
@@ -310,11 +317,17 @@ static int init_ctx(const sbli_params* p, void* hip_stream, bool in_batch, sbli_
     if (e == hipSuccess) e = hipMalloc((void**)&x->diag_out, sizeof(double) * 10);
     if (e == hipSuccess) e = hipMalloc(&x->inst_dev, sizeof(BoxInst<double>));
     if (e == hipSuccess && num_fused(x) > 0) {
-        if (!in_batch && prefers_staged(p, x->r) && ensure_staged_scratch(x) == hipSuccess) {
-            x->variant = num_fused(x);
-        } else {
-            (void)hipGetLastError();   // of the scratch: the fused form runs without it
-            choose_fused(p->dtype, x->r, p, 1, &x->variant, &x->zchunk);
+        choose_fused(p->dtype, x->r, p, 1, &x->variant, &x->zchunk);
+        if (!in_batch && prefers_staged(p, x->r)) {
+            if (ensure_staged_scratch(x) == hipSuccess) {
+                x->by_rule = true;
+                x->graph_variant = x->variant;
+                x->graph_zchunk = x->zchunk;
+                x->variant = num_fused(x);
+                x->zchunk = p->nz;
+            } else {
+                (void)hipGetLastError();   // the fused form runs without the scratch
+            }
         }
     }
     if (e == hipSuccess) e = update_table(x);
@@ -381,12 +394,27 @@ extern "C" int sbli_tgv_init(sbli_ctx* ctx, void* q, const double* phase) {
     return SBLI_OK;
 }
 
-// Enqueues one residual / stage launch of the selected variant.  The staged
+// The variant that a call launches: the selected one, except that a call recorded into a
+// graph keeps to the fused form where the staged form is only sbli_init's choice.  Graphs
+// of one context can be replayed on several streams at a time, and their nested fields
+// would share the context's scratch; the bits are the same.
+static int launch_variant(const sbli_ctx* ctx) {
+    if (!ctx->by_rule || !is_staged(ctx, ctx->variant)) return ctx->variant;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) {
+        (void)hipGetLastError();   // the default stream while another one captures: not recorded
+        return ctx->variant;
+    }
+    return status == hipStreamCaptureStatusActive ? ctx->graph_variant : ctx->variant;
+}
+
+// Enqueues one residual / stage launch of variant v (see launch_variant).  The staged
 // form's scratch exists whenever it is selected (update_table allocates it and
 // a failed allocation leaves the previous variant selected); it is checked
 // again here so that no launch ever runs without it.
-static int launch_any(sbli_ctx* ctx, const void* qin, void* dq, void* qout, int mode, double dt, double A, double B) {
-    if (is_staged(ctx, ctx->variant)) {
+static int launch_any(sbli_ctx* ctx, int v, const void* qin, void* dq, void* qout, int mode, double dt, double A,
+                      double B) {
+    if (is_staged(ctx, v)) {
         if (!ctx->stg) return fail(ctx, SBLI_ERR_ALLOC, "stage launch: the staged form's scratch is not allocated");
         const bool f64 = ctx->p.dtype == SBLI_F64;
         const StagedArgs a{ctx->stream, f64, ctx->r, f64 ? (const void*)&ctx->c64 : (const void*)&ctx->c32,
@@ -398,9 +426,9 @@ static int launch_any(sbli_ctx* ctx, const void* qin, void* dq, void* qout, int 
     const int sym = ctx->p.bc[0] | ctx->p.bc[1] | ctx->p.bc[2];
     const StageArgs a{ctx->stream, ctx->inst_dev, 1, total_wg(ctx), mode, dt, A, B, sym};
     if (ctx->p.dtype == SBLI_F64)
-        StageDispatch<double>::launch(ctx->r, ctx->variant, a, (const double*)qin, (double*)dq, (double*)qout);
+        StageDispatch<double>::launch(ctx->r, v, a, (const double*)qin, (double*)dq, (double*)qout);
     else
-        StageDispatch<float>::launch(ctx->r, ctx->variant, a, (const float*)qin, (float*)dq, (float*)qout);
+        StageDispatch<float>::launch(ctx->r, v, a, (const float*)qin, (float*)dq, (float*)qout);
     return SBLI_OK;
 }
 
@@ -409,7 +437,7 @@ extern "C" int sbli_rhs(sbli_ctx* ctx, const void* q, void* rhs) {
     if (!q || !rhs) return fail(ctx, SBLI_ERR_ARG, "sbli_rhs: NULL state pointer");
     const size_t bytes = 5 * (size_t)npoints(ctx) * elem_size(ctx);
     if (overlaps(q, rhs, bytes)) return fail(ctx, SBLI_ERR_ARG, "sbli_rhs: q and rhs overlap");
-    const int rc = launch_any(ctx, q, nullptr, rhs, kModeRHS, 0.0, 0.0, 0.0);
+    const int rc = launch_any(ctx, launch_variant(ctx), q, nullptr, rhs, kModeRHS, 0.0, 0.0, 0.0);
     if (rc != SBLI_OK) return rc;
     HIP_TRY(ctx, hipGetLastError());
     return SBLI_OK;
@@ -425,6 +453,7 @@ static int enqueue_steps(sbli_ctx* ctx, void* a, void* b, void* dq, double dt, i
     void* src = a;
     void* dst = b;
     *result = a;
+    const int v = launch_variant(ctx);
     for (int s = 0; s < nsteps; ++s) {
         for (int k = 0; k < 3; ++k) {
             if (ctx->net) {
@@ -436,7 +465,7 @@ static int enqueue_steps(sbli_ctx* ctx, void* a, void* b, void* dq, double dt, i
                 if (rc != SBLI_OK)
                     return fail(ctx, rc, "closure evaluation failed: %s", sbli_net_last_error(ctx->net));
             }
-            const int rc = launch_any(ctx, src, dq, dst, kModeStage1 + k, dt, kRK_A[k], kRK_B[k]);
+            const int rc = launch_any(ctx, v, src, dq, dst, kModeStage1 + k, dt, kRK_A[k], kRK_B[k]);
             if (rc != SBLI_OK) return rc;
             void* t = src;
             src = dst;
@@ -532,12 +561,15 @@ extern "C" int sbli_set_tuning(sbli_ctx* ctx, int variant, int zchunk) {
     if (zchunk < 1 || zchunk > ctx->p.nz)
         return fail(ctx, SBLI_ERR_ARG, "sbli_set_tuning: zchunk %d out of range [1, %d]", zchunk, ctx->p.nz);
     const int old_v = ctx->variant, old_z = ctx->zchunk;
+    const bool old_rule = ctx->by_rule;
     ctx->variant = variant;
     ctx->zchunk = zchunk;
+    ctx->by_rule = false;
     const hipError_t e = update_table(ctx);
     if (e != hipSuccess) {
         ctx->variant = old_v;
         ctx->zchunk = old_z;
+        ctx->by_rule = old_rule;
         (void)update_table(ctx);   // the previous configuration, rebuilt after the reported failure
         return fail(ctx, e == hipErrorOutOfMemory ? SBLI_ERR_ALLOC : SBLI_ERR_HIP, "sbli_set_tuning: %s",
                     hipGetErrorString(e));
@@ -575,6 +607,8 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
     HIP_TRY(ctx, hipEventCreate(&e1));
     float best = 1e30f;
     int bv = ctx->variant, bz = ctx->zchunk;
+    const bool old_rule = ctx->by_rule;
+    ctx->by_rule = false;
     for (int v = 0; v < num_variants(ctx); ++v) {
         // the staged form has no z-chunks; it is skipped when its scratch cannot be allocated
         int nv = is_staged(ctx, v) ? 1 : nc;
@@ -604,6 +638,7 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
                 (void)hipEventDestroy(e1);
                 ctx->variant = bv;
                 ctx->zchunk = bz;
+                ctx->by_rule = old_rule && best == 1e30f;
                 (void)update_table(ctx);
                 if (rc != SBLI_OK) return rc;
                 return fail(ctx, SBLI_ERR_HIP, "sbli_autotune: %s", hipGetErrorString(err));
