@@ -10,8 +10,10 @@
  *    SBLI_ERR_* code otherwise.  No call aborts the process; after an error,
  *    sbli_last_error() returns a human-readable message for that context.
  *  - Memory: the caller allocates and owns every state-sized buffer; all state
- *    pointers are DEVICE pointers.  The library owns only the context and small
- *    device scratch (reduction partials), allocated in sbli_init.
+ *    pointers are DEVICE pointers.  The library owns only the context and device
+ *    scratch, allocated in sbli_init: reduction partials and, where the staged
+ *    form of the stage kernel is selected (see the launch tuning below), six
+ *    words a point; sbli_set_tuning and sbli_autotune may allocate that later.
  *  - Layout of a state q: five fields back to back, q[f][z][y][x], x fastest,
  *    f = (rho, rho*u, rho*v, rho*w, rho*E); element type double (SBLI_F64) or
  *    float (SBLI_F32) as chosen at init; nx*ny*nz*5 elements.
@@ -150,7 +152,9 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  * have only this variant.  All variants compute bitwise identical results; only speed
  * differs.  sbli_init selects a variant and a zchunk by the grid's size: the staged form
  * for orders 6 (FP32: up to 96^3 points) and 8 while its scratch is at most 1/64 of the
- * device's free memory, else a fused variant and a zchunk that fill the device.
+ * device's free memory and that of all contexts that took it this way at most 1/64 of the
+ * device's memory, else a fused variant and a zchunk that fill the device (sbli_set_tuning
+ * selects the staged form for a larger grid).
  *
  * Graphs: sbli_rhs and sbli_rk3_step may be captured (the context's stream capturing).  The
  * staged form's scratch belongs to the context, so what is recorded with it must not run

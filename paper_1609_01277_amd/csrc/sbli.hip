@@ -33,6 +33,7 @@ struct sbli_ctx {
     int variant;            // index into the compiled stage variants of (dtype, order)
     bool by_rule;           // the staged form is sbli_init's choice, not the caller's:
     int graph_variant, graph_zchunk;   // graphs then record this fused configuration
+    size_t rule_bytes;      // scratch counted against the device's share for such choices
     BoxInst<double> inst64; // launch table entry (host copy) of the box
     BoxInst<float> inst32;
     void* inst_dev;         // the same entry on the device
@@ -213,19 +214,50 @@ static void choose_fused(int dtype, int r, const sbli_params* p, int count, int*
 // order 6, 32^3: 25, 14; 64^3: 64, 28; 128^3: 377, 147; 256^3: 2,998, 1,042; FP32 order 8:
 // 27, 13; 50, 23; 221, 119; 1,629, 772).  FP32 order 6: up to about 96^3 (17, 13; 27, 21;
 // 96^3: 55, 46; 128^3: 93, 102; 256^3: 612, 770).  Not at orders 2 and 4 (FP64 order 4:
-// 12, 13; 23, 25; 91, 166; 592, 1,230).  Its scratch is allocated with the context, so a
-// grid only defaults to it while that is a small part of the free memory: a program that
-// fills the device with states is not made to run out of it.
-static bool prefers_staged(const sbli_params* p, int r) {
-    const int64_t P = (int64_t)p->nx * p->ny * p->nz;
-    if (r < 3 || (r == 3 && p->dtype == SBLI_F32 && P > 96 * 96 * 96)) return false;
+// 12, 13; 23, 25; 91, 166; 592, 1,230).  Its scratch is allocated with the context and no
+// caller asked for it, so a context only defaults to it while that is at most 1/64 of the
+// free memory, and the scratch of all contexts that did is at most 1/64 of the device's
+// memory (4.5 GB of 288): a program that fills the device with states, of one solver or of
+// many, is not made to run out of it.
+constexpr int kRuleShare = 64;
+
+// Bytes of scratch that contexts hold by the rule, per device.
+struct RuleScratch {
+    static constexpr int kDevices = 64;
+    std::mutex lock;
+    size_t held[kDevices] = {};
+    // Reserves `bytes` of the device's share; false if they do not fit.
+    bool take(int device, size_t bytes, size_t share) {
+        std::lock_guard<std::mutex> g(lock);
+        if (device >= kDevices || held[device] + bytes > share) return false;
+        held[device] += bytes;
+        return true;
+    }
+    void give(int device, size_t bytes) {
+        std::lock_guard<std::mutex> g(lock);
+        held[device] -= bytes;
+    }
+};
+static RuleScratch g_rule_scratch;
+
+// Whether the context defaults to the staged form; its scratch is then allocated and counted.
+static bool take_staged(sbli_ctx* x) {
+    const int64_t P = npoints(x);
+    if (x->r < 3 || (x->r == 3 && x->p.dtype == SBLI_F32 && P > 96 * 96 * 96)) return false;
     size_t free_b = 0, total = 0;
     if (hipMemGetInfo(&free_b, &total) != hipSuccess) {
         (void)hipGetLastError();   // the fused form needs no scratch
         return false;
     }
-    const double scratch = (double)kStagedScratchWords * P * (p->dtype == SBLI_F64 ? 8 : 4);
-    return scratch <= free_b / 64.0;
+    const size_t bytes = (size_t)kStagedScratchWords * P * elem_size(x);
+    if (bytes > free_b / kRuleShare || !g_rule_scratch.take(x->device, bytes, total / kRuleShare)) return false;
+    if (ensure_staged_scratch(x) != hipSuccess) {
+        (void)hipGetLastError();   // the fused form runs without the scratch
+        g_rule_scratch.give(x->device, bytes);
+        return false;
+    }
+    x->rule_bytes = bytes;
+    return true;
 }
 
 // Rebuilds the box's launch-table entry for the fused configuration in use (the current
@@ -318,16 +350,12 @@ static int init_ctx(const sbli_params* p, void* hip_stream, bool in_batch, sbli_
     if (e == hipSuccess) e = hipMalloc(&x->inst_dev, sizeof(BoxInst<double>));
     if (e == hipSuccess && num_fused(x) > 0) {
         choose_fused(p->dtype, x->r, p, 1, &x->variant, &x->zchunk);
-        if (!in_batch && prefers_staged(p, x->r)) {
-            if (ensure_staged_scratch(x) == hipSuccess) {
-                x->by_rule = true;
-                x->graph_variant = x->variant;
-                x->graph_zchunk = x->zchunk;
-                x->variant = num_fused(x);
-                x->zchunk = p->nz;
-            } else {
-                (void)hipGetLastError();   // the fused form runs without the scratch
-            }
+        if (!in_batch && take_staged(x)) {
+            x->by_rule = true;
+            x->graph_variant = x->variant;
+            x->graph_zchunk = x->zchunk;
+            x->variant = num_fused(x);
+            x->zchunk = p->nz;
         }
     }
     if (e == hipSuccess) e = update_table(x);
@@ -347,6 +375,7 @@ static int init_ctx(const sbli_params* p, void* hip_stream, bool in_batch, sbli_
         (void)hipFree(x->diag_out);
         (void)hipFree(x->inst_dev);
         (void)hipFree(x->stg);
+        if (x->rule_bytes) g_rule_scratch.give(x->device, x->rule_bytes);
         delete x;
         return code;
     }
@@ -367,6 +396,7 @@ extern "C" int sbli_destroy(sbli_ctx* ctx) {
         const hipError_t e = hipFree(p);
         if (first == hipSuccess) first = e;
     }
+    if (ctx->rule_bytes) g_rule_scratch.give(ctx->device, ctx->rule_bytes);
     delete ctx;
     if (first != hipSuccess) return fail(nullptr, SBLI_ERR_HIP, "sbli_destroy: %s", hipGetErrorString(first));
     return SBLI_OK;
