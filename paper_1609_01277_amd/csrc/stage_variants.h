@@ -18,19 +18,22 @@ struct StageVariant {
     int zl;     // 1: the R planes below the output plane in LDS instead of registers
 };
 
-// X-macro lists of (TX, TY, PRE, RT, MINW, DB, ZL) per (type, radius).
+// X-macro lists of (TX, TY, PRE, RT, MINW, DB, ZL) per (type, radius).  An index is what
+// sbli_set_tuning takes and callers store: entries keep their places, new ones go at the end.
 #define SBLI_VARIANTS_D1(X) \
-    X(16, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0)
-#define SBLI_VARIANTS_D2(X) \
-    X(16, 16, 1, 1, 1, 2, 0) X(16, 8, 1, 1, 2, 2, 0) X(16, 16, 1, 1, 1, 1, 0) X(16, 8, 1, 1, 2, 0, 0)
+    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0) X(16, 16, 1, 1, 1, 1, 0)
+#define SBLI_VARIANTS_D2(X)                                                                                    \
+    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(16, 16, 0, 1, 1, 0, 0) X(32, 8, 0, 0, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0) \
+    X(16, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 0, 1, 1, 0) X(16, 16, 1, 1, 1, 2, 0) X(16, 8, 1, 1, 2, 2, 0)
 #define SBLI_VARIANTS_D3(X) X(8, 8, 0, 0, 1, 0, 0) X(8, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 1, 0)
 #define SBLI_VARIANTS_D4(X) \
     X(16, 4, 0, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 0) X(8, 8, 0, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 1) X(8, 8, 1, 0, 1, 0, 1)
 #define SBLI_VARIANTS_F1(X) \
     X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 1, 0)
-#define SBLI_VARIANTS_F2(X)                                                                                 \
-    X(32, 16, 1, 1, 1, 1, 0) X(32, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 1, 1, 0)            \
-    X(16, 16, 1, 1, 1, 2, 0) X(16, 8, 1, 1, 1, 0, 0)
+#define SBLI_VARIANTS_F2(X)                                                                                   \
+    X(16, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 1, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 3, 0, 0) \
+    X(16, 16, 1, 1, 3, 0, 0) X(16, 16, 1, 1, 1, 1, 0) X(32, 8, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 3, 1, 0)            \
+    X(32, 16, 1, 1, 1, 0, 0) X(32, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 1, 2, 0)
 #define SBLI_VARIANTS_F3(X) \
     X(16, 16, 0, 0, 1, 0, 0) X(16, 16, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 2, 0)
 #define SBLI_VARIANTS_F4(X) X(16, 8, 0, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 0)
