@@ -174,11 +174,12 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  *   zchunk).  sbli_set_tuning waits for the context's stream (it updates a small
  *   device table).  Selecting the staged form may allocate its scratch
  *   (SBLI_ERR_ALLOC if that fails; the previous selection then stays).
- * sbli_autotune: time every variant with several zchunks, the one sbli_init's rule would give it among them (hipEvents on the
+ * sbli_autotune: time the selection at the call, then every variant with several zchunks,
+ *   the one sbli_init's rule would give it among them (hipEvents on the
  *   context's stream, `reps` RK3 steps each after one warm-up step) using the
  *   caller's device buffers, then select the fastest (a later candidate replaces
  *   the best so far only when more than 1 % faster, so near-ties resolve to the
- *   earlier variant and the longer zchunk); *best_ms (may be NULL) receives the
+ *   selection at the call, the earlier variant and the longer zchunk); *best_ms (may be NULL) receives the
  *   selected candidate's time per step.  The contents of q, q_tmp and dq afterwards are
  *   unspecified (they are advanced in time).  Synchronises the stream.
  */
@@ -216,6 +217,8 @@ int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, double dt, int 
  *   returns SBLI_ERR_NONFINITE if any box is flagged.  Synchronises the stream.
  * sbli_batch_set_tuning / get_tuning / autotune: variant (as for a single box)
  *   and the cap on z-planes per workgroup (zmax); changing them drops the graph.
+ *   Where workgroups of zmax planes would leave compute units idle, they take fewer.
+ *   autotune times every variant with zmax 128 to 16, and the selection at the call.
  * In all calls q, q_tmp, dq are distinct device buffers of offsets[count]
  * elements; the result is in q.
  */

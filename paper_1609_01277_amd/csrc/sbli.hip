@@ -134,81 +134,6 @@ static hipError_t ensure_staged_scratch(sbli_ctx* x) {
     return hipMalloc(&x->stg, (size_t)kStagedScratchWords * (size_t)npoints(x) * elem_size(x));
 }
 
-// Default launch configuration.  A workgroup of the fused kernel takes zchunk + 4R serial
-// steps of one plane, and the chip runs 256 workgroups at a time; its time is modelled as
-// (zchunk + 4R) plane_us (1 + beside (rounds - 1)), rounds = ceil(workgroups / 256): a
-// small grid takes chunks of a few planes (32^3: of one), a large one the longest that
-// still fill the last round.  Each (type, radius) has one or two variants to choose from,
-// a small tile for small grids and the one that is fastest on large grids; `beside` < 1
-// where two workgroups fit a CU.  Within 15 % of the fastest of all variants and chunks
-// from 20^3 to 256^3.  Measured us a stage, first variant with chunks of 32
-// planes or the whole grid -> this choice (and the fastest of all variants and chunks),
-// FP64 order 4: 32^3 71 -> 12 (12), 64^3 76 -> 24 (24), 96^3 66 -> 47 (47), 160^3 237 ->
-// 179 (179), 256^3 742 -> 592 (592); FP32 order 4: 75 -> 11 (11), 78 -> 18 (18), 69 -> 34
-// (34), 127 -> 98 (98), 392 -> 335 (335).
-struct LaunchCand {
-    int variant;        // index into the variant list of (type, radius)
-    double plane_us;    // a workgroup's time for a plane with a CU to itself
-    double beside;      // cost of a further round relative to the first
-};
-
-static const LaunchCand* launch_cands(int dtype, int r, int& n) {
-    static const LaunchCand d1[] = {{3, 1.2, 0.8}, {2, 1.6, 0.8}}, d2[] = {{8, 1.35, 0.75}, {7, 1.7, 1.0}},
-                            d3[] = {{1, 2.0, 1.0}}, d4[] = {{4, 2.4, 1.0}}, f1[] = {{3, 0.9, 0.8}, {2, 1.2, 0.8}},
-                            f2[] = {{11, 1.4, 1.0}, {10, 1.95, 1.0}}, f3[] = {{3, 1.5, 1.0}}, f4[] = {{2, 1.9, 0.35}};
-    const bool d = dtype == SBLI_F64;
-    n = r <= 2 ? 2 : 1;
-    switch (r) {
-        case 1: return d ? d1 : f1;
-        case 2: return d ? d2 : f2;
-        case 3: return d ? d3 : f3;
-        default: return d ? d4 : f4;
-    }
-}
-
-static StageVariant fused_variant(int dtype, int r, int v) {
-    return dtype == SBLI_F64 ? StageDispatch<double>::get(r, v) : StageDispatch<float>::get(r, v);
-}
-
-constexpr int kCus = 256;
-
-// The chunk that makes the modelled time of variant v over `count` boxes least; *cost
-// receives it (in plane times).
-static int best_zchunk(int dtype, int r, int v, double beside, const sbli_params* p, int count, double* cost) {
-    const StageVariant sv = fused_variant(dtype, r, v);
-    int zmax = 1, best = 1;
-    for (int i = 0; i < count; ++i) zmax = std::max(zmax, p[i].nz);
-    *cost = HUGE_VAL;
-    for (int zc = 1; zc <= zmax; ++zc) {
-        double units = 0;
-        for (int i = 0; i < count; ++i)
-            units += (double)((p[i].nx + sv.tx - 1) / sv.tx) * ((p[i].ny + sv.ty - 1) / sv.ty) *
-                     ((p[i].nz + zc - 1) / zc);
-        const double rounds = std::max(1.0, std::ceil(units / kCus));
-        const double t = (zc + 4 * r) * (1.0 + beside * (rounds - 1.0));
-        if (t < *cost) {
-            *cost = t;
-            best = zc;
-        }
-    }
-    return best;
-}
-
-static void choose_fused(int dtype, int r, const sbli_params* p, int count, int* variant, int* zchunk) {
-    int n = 0;
-    const LaunchCand* c = launch_cands(dtype, r, n);
-    double least = HUGE_VAL;
-    for (int k = 0; k < n; ++k) {
-        double t = 0;
-        const int zc = best_zchunk(dtype, r, c[k].variant, c[k].beside, p, count, &t);
-        if (t * c[k].plane_us < least) {
-            least = t * c[k].plane_us;
-            *variant = c[k].variant;
-            *zchunk = zc;
-        }
-    }
-}
-
 // Where the staged form is the default.  Order 8, and order 6 in FP64: it is the faster
 // one on every grid (us a stage, fused in its best configuration against staged: FP64
 // order 6, 32^3: 25, 14; 64^3: 64, 28; 128^3: 377, 147; 256^3: 2,998, 1,042; FP32 order 8:
@@ -625,13 +550,14 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
     const size_t bytes = 5 * (size_t)npoints(ctx) * elem_size(ctx);
     if (overlaps(q, q_tmp, bytes) || overlaps(q, dq, bytes) || overlaps(q_tmp, dq, bytes))
         return fail(ctx, SBLI_ERR_ARG, "sbli_autotune: q, q_tmp and dq must not overlap");
-    const int nz = ctx->p.nz;
-    int cands[8], nc = 0;
-    for (int zc = nz; zc >= 16 && nc < 6; zc = (zc + 1) / 2) {
-        cands[nc++] = zc;
-        if (zc == 16) break;
-    }
-    if (nc == 0) cands[nc++] = nz;
+    // The configuration in use is timed first, so the search cannot end on a slower one; the
+    // staged form is skipped when its scratch cannot be allocated.
+    const Launch entry{ctx->variant, ctx->zchunk}, staged{num_fused(ctx), ctx->p.nz};
+    Launch cands[kMaxTried + 1];
+    int nc = 0;
+    if (is_staged(ctx, entry.variant)) cands[nc++] = entry;
+    if (num_fused(ctx) > 0) nc += tuning_candidates(ctx->p.dtype, ctx->r, &ctx->p, entry, cands + nc);
+    if (!is_staged(ctx, entry.variant)) cands[nc++] = staged;
     hipEvent_t e0, e1;
     HIP_TRY(ctx, hipEventCreate(&e0));
     HIP_TRY(ctx, hipEventCreate(&e1));
@@ -639,45 +565,36 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
     int bv = ctx->variant, bz = ctx->zchunk;
     const bool old_rule = ctx->by_rule;
     ctx->by_rule = false;
-    for (int v = 0; v < num_variants(ctx); ++v) {
-        // the staged form has no z-chunks; it is skipped when its scratch cannot be allocated
-        int nv = is_staged(ctx, v) ? 1 : nc;
-        if (!is_staged(ctx, v)) {   // and the chunk that the launch model prefers
-            double t;
-            const int zc = best_zchunk(ctx->p.dtype, ctx->r, v, 1.0, &ctx->p, 1, &t);
-            if (std::find(cands, cands + nc, zc) == cands + nc) cands[nv++] = zc;
+    for (int ci = 0; ci < nc; ++ci) {
+        ctx->variant = cands[ci].variant;
+        ctx->zchunk = cands[ci].zchunk;
+        if (update_table(ctx) != hipSuccess) {
+            (void)hipGetLastError();
+            continue;
         }
-        for (int ci = 0; ci < nv; ++ci) {
-            ctx->variant = v;
-            ctx->zchunk = cands[ci];
-            if (update_table(ctx) != hipSuccess) {
-                (void)hipGetLastError();
-                continue;
-            }
-            void* res = nullptr;
-            int rc = enqueue_steps(ctx, q, q_tmp, dq, dt, 1, &res);          // warm-up
-            hipError_t err = hipEventRecord(e0, ctx->stream);
-            if (rc == SBLI_OK && err == hipSuccess) rc = enqueue_steps(ctx, q, q_tmp, dq, dt, reps, &res);
-            if (err == hipSuccess) err = hipEventRecord(e1, ctx->stream);
-            if (err == hipSuccess) err = hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (err == hipSuccess && rc == SBLI_OK) err = hipEventElapsedTime(&ms, e0, e1);
-            if (err != hipSuccess || rc != SBLI_OK) {
-                // cleanup after the failure reported below
-                (void)hipEventDestroy(e0);
-                (void)hipEventDestroy(e1);
-                ctx->variant = bv;
-                ctx->zchunk = bz;
-                ctx->by_rule = old_rule && best == 1e30f;
-                (void)update_table(ctx);
-                if (rc != SBLI_OK) return rc;
-                return fail(ctx, SBLI_ERR_HIP, "sbli_autotune: %s", hipGetErrorString(err));
-            }
-            if (ms < best * kTuneMargin) {
-                best = ms;
-                bv = v;
-                bz = cands[ci];
-            }
+        void* res = nullptr;
+        int rc = enqueue_steps(ctx, q, q_tmp, dq, dt, 1, &res);          // warm-up
+        hipError_t err = hipEventRecord(e0, ctx->stream);
+        if (rc == SBLI_OK && err == hipSuccess) rc = enqueue_steps(ctx, q, q_tmp, dq, dt, reps, &res);
+        if (err == hipSuccess) err = hipEventRecord(e1, ctx->stream);
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (err == hipSuccess && rc == SBLI_OK) err = hipEventElapsedTime(&ms, e0, e1);
+        if (err != hipSuccess || rc != SBLI_OK) {
+            // cleanup after the failure reported below
+            (void)hipEventDestroy(e0);
+            (void)hipEventDestroy(e1);
+            ctx->variant = bv;
+            ctx->zchunk = bz;
+            ctx->by_rule = old_rule && best == 1e30f;
+            (void)update_table(ctx);
+            if (rc != SBLI_OK) return rc;
+            return fail(ctx, SBLI_ERR_HIP, "sbli_autotune: %s", hipGetErrorString(err));
+        }
+        if (ms < best * kTuneMargin) {
+            best = ms;
+            bv = cands[ci].variant;
+            bz = cands[ci].zchunk;
         }
     }
     const hipError_t d0 = hipEventDestroy(e0), d1 = hipEventDestroy(e1);
@@ -706,6 +623,7 @@ struct sbli_batch {
     hipStream_t cap = nullptr;              // internal stream used only for graph capture
     std::vector<sbli_ctx*> ctx;             // one context per box (constants, diagnostics scratch)
     std::vector<sbli_instance> inst;
+    std::vector<sbli_params> box;           // the boxes as the launch rule takes them
     std::vector<size_t> off;                // element offsets, count + 1 entries
     int variant = 0, zmax = 64;
     std::vector<BoxInst<double>> t64;
@@ -760,9 +678,10 @@ static int batch_build_table(sbli_batch* b) {
     // Chunks of one length within a box, and the boxes with the longest chunks first, so
     // that the launch does not end on them.  With the XCDs taking turns (fused_stage_kernel)
     // ten steps of 64 FP32 boxes of 32 to 128 points go from 24.6 to 23.0 ms.
+    const int zmax = capped_chunk(b->dtype, b->r, b->variant, b->box.data(), b->count, b->zmax);
     std::vector<int> zc(b->count), by_len(b->count);
     for (int i = 0; i < b->count; ++i) {
-        const int n = b->inst[i].n, chunks = (n + std::min(n, b->zmax) - 1) / std::min(n, b->zmax);
+        const int n = b->inst[i].n, chunks = (n + std::min(n, zmax) - 1) / std::min(n, zmax);
         zc[i] = (n + chunks - 1) / chunks;
         by_len[i] = i;
     }
@@ -874,7 +793,6 @@ extern "C" int sbli_batch_init(const sbli_instance* inst, int count, int order, 
     b->stream = (hipStream_t)hip_stream;
     b->inst.assign(inst, inst + count);
     b->off.assign(count + 1, 0);
-    std::vector<sbli_params> box_params;
     for (int i = 0; i < count; ++i) {
         sbli_params p{inst[i].n, inst[i].n, inst[i].n, 2 * M_PI, 2 * M_PI, 2 * M_PI, inst[i].Re, inst[i].Mach,
                       inst[i].Pr, inst[i].gamma, order, dtype};
@@ -886,7 +804,7 @@ extern "C" int sbli_batch_init(const sbli_instance* inst, int count, int order, 
             return rc;
         }
         b->ctx.push_back(c);
-        box_params.push_back(p);
+        b->box.push_back(p);
         b->off[i + 1] = b->off[i] + 5 * (size_t)inst[i].n * inst[i].n * inst[i].n;
     }
     hipError_t e = hipMalloc(&b->table_dev, sizeof(BoxInst<double>) * count);
@@ -896,7 +814,7 @@ extern "C" int sbli_batch_init(const sbli_instance* inst, int count, int order, 
         sbli_batch_destroy(b);
         return SBLI_ERR_HIP;
     }
-    choose_fused(dtype, b->r, box_params.data(), count, &b->variant, &b->zmax);
+    choose_fused(dtype, b->r, b->box.data(), count, &b->variant, &b->zmax);
     int rc = batch_build_table(b);
     if (rc != SBLI_OK) {
         g_batch_err = b->err;
@@ -1018,39 +936,38 @@ extern "C" int sbli_batch_autotune(sbli_batch* b, void* q, void* q_tmp, void* dq
     int rc = batch_check_buffers(b, "sbli_batch_autotune", q, q_tmp, dq);
     if (rc != SBLI_OK) return rc;
     if (reps < 1) return bfail(b, SBLI_ERR_ARG, "sbli_batch_autotune: reps must be >= 1");
-    const int nv = b->dtype == SBLI_F64 ? StageDispatch<double>::count(b->r) : StageDispatch<float>::count(b->r);
-    const int zc[6] = {128, 96, 64, 48, 32, 16};
+    Launch cands[kMaxTried];
+    const int nc = batch_candidates(b->dtype, b->r, b->box.data(), b->count, {b->variant, b->zmax}, cands);
     hipEvent_t e0, e1;
     BHIP_TRY(b, hipEventCreate(&e0));
     BHIP_TRY(b, hipEventCreate(&e1));
     float best = 1e30f;
     int bv = b->variant, bz = b->zmax;
     hipError_t err = hipSuccess;
-    // a failure ends both loops; rc and err then hold it
-    for (int v = 0; v < nv && rc == SBLI_OK && err == hipSuccess; ++v)
-        for (int zi = 0; zi < 6; ++zi) {
-            b->variant = v;
-            b->zmax = zc[zi];
-            rc = batch_build_table(b);
-            if (rc != SBLI_OK) break;
-            batch_enqueue(b, b->stream, q, q_tmp, dq, 1);
+    // a failure ends the loop; rc and err then hold it
+    for (int ci = 0; ci < nc; ++ci) {
+        b->variant = cands[ci].variant;
+        b->zmax = cands[ci].zchunk;
+        rc = batch_build_table(b);
+        if (rc != SBLI_OK) break;
+        batch_enqueue(b, b->stream, q, q_tmp, dq, 1);
+        err = hipGetLastError();
+        if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
+        if (err == hipSuccess) {
+            batch_enqueue(b, b->stream, q, q_tmp, dq, reps);
             err = hipGetLastError();
-            if (err == hipSuccess) err = hipEventRecord(e0, b->stream);
-            if (err == hipSuccess) {
-                batch_enqueue(b, b->stream, q, q_tmp, dq, reps);
-                err = hipGetLastError();
-            }
-            if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
-            if (err == hipSuccess) err = hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-            if (err != hipSuccess) break;
-            if (ms < best * kTuneMargin) {
-                best = ms;
-                bv = v;
-                bz = zc[zi];
-            }
         }
+        if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+        if (err != hipSuccess) break;
+        if (ms < best * kTuneMargin) {
+            best = ms;
+            bv = cands[ci].variant;
+            bz = cands[ci].zchunk;
+        }
+    }
     const hipError_t d0 = hipEventDestroy(e0), d1 = hipEventDestroy(e1);
     if (err == hipSuccess) err = d0 != hipSuccess ? d0 : d1;
     b->variant = bv;

@@ -7,36 +7,9 @@
 #pragma once
 
 #include "kernels_stage_fused.h"
+#include "launch_rule.h"
 
 namespace sbli {
-
-struct StageVariant {
-    int tx, ty, pre, rot;
-    int minw;   // wavefronts per SIMD the register allocation must allow (1 = as many VGPRs as needed)
-    int db;     // barrier schedule: 0 two barriers a plane, 1 one, 2 one and the work split between
-                // column and plane wavefronts (kernels_stage_fused.h)
-    int zl;     // 1: the R planes below the output plane in LDS instead of registers
-};
-
-// X-macro lists of (TX, TY, PRE, RT, MINW, DB, ZL) per (type, radius).  An index is what
-// sbli_set_tuning takes and callers store: entries keep their places, new ones go at the end.
-#define SBLI_VARIANTS_D1(X) \
-    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0) X(16, 16, 1, 1, 1, 1, 0)
-#define SBLI_VARIANTS_D2(X)                                                                                    \
-    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(16, 16, 0, 1, 1, 0, 0) X(32, 8, 0, 0, 1, 0, 0) X(16, 8, 1, 1, 2, 0, 0) \
-    X(16, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 0, 1, 1, 0) X(16, 16, 1, 1, 1, 2, 0) X(16, 8, 1, 1, 2, 2, 0)
-#define SBLI_VARIANTS_D3(X) X(8, 8, 0, 0, 1, 0, 0) X(8, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 1, 0)
-#define SBLI_VARIANTS_D4(X) \
-    X(16, 4, 0, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 0) X(8, 8, 0, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 1) X(8, 8, 1, 0, 1, 0, 1)
-#define SBLI_VARIANTS_F1(X) \
-    X(16, 16, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 1, 0)
-#define SBLI_VARIANTS_F2(X)                                                                                   \
-    X(16, 8, 1, 0, 1, 0, 0) X(16, 8, 1, 1, 1, 0, 0) X(16, 16, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 1, 0, 0) X(32, 8, 1, 1, 3, 0, 0) \
-    X(16, 16, 1, 1, 3, 0, 0) X(16, 16, 1, 1, 1, 1, 0) X(32, 8, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 3, 1, 0)            \
-    X(32, 16, 1, 1, 1, 0, 0) X(32, 16, 1, 1, 1, 1, 0) X(16, 16, 1, 1, 1, 2, 0)
-#define SBLI_VARIANTS_F3(X) \
-    X(16, 16, 0, 0, 1, 0, 0) X(16, 16, 1, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 16, 1, 1, 1, 2, 0)
-#define SBLI_VARIANTS_F4(X) X(16, 8, 0, 0, 1, 0, 0) X(16, 8, 1, 0, 1, 0, 0) X(16, 4, 1, 0, 1, 0, 0)
 
 // One launch: the boxes (device table), their total workgroup count, the mode
 // and the RK coefficients.
@@ -75,7 +48,6 @@ inline bool try_variant(int& k, int want, const StageArgs& a, const T* qin, T* d
 
 #define SBLI_TRY(TX_, TY_, PRE_, RT_, MINW_, DB_, ZL_) \
     if (try_variant<T, R, TX_, TY_, PRE_, RT_, MINW_, DB_, ZL_>(k, v, a, qin, dq, qout)) return true;
-#define SBLI_ENTRY(TX_, TY_, PRE_, RT_, MINW_, DB_, ZL_) StageVariant{TX_, TY_, PRE_, RT_, MINW_, DB_, ZL_},
 
 template <typename T, int R>
 struct VariantSet;
@@ -83,30 +55,22 @@ struct VariantSet;
 // The launch function of a (type, radius) -- which instantiates its kernels --
 // is defined only in the translation unit stage_{f64,f32}_r{1..4}.hip that sets
 // SBLI_STAGE_TU_{TYPE,R,LIST}, so the variants compile in parallel.
-#define SBLI_VARIANT_SET(TYPE, RR, LIST)                                                                  \
+#define SBLI_VARIANT_SET(TYPE, RR)                                                                        \
     template <>                                                                                           \
     struct VariantSet<TYPE, RR> {                                                                         \
         using T = TYPE;                                                                                   \
         static constexpr int R = RR;                                                                      \
-        static int count() {                                                                              \
-            static const StageVariant t[] = {LIST(SBLI_ENTRY)};                                          \
-            return (int)(sizeof(t) / sizeof(t[0]));                                                       \
-        }                                                                                                 \
-        static StageVariant get(int i) {                                                                  \
-            static const StageVariant t[] = {LIST(SBLI_ENTRY)};                                          \
-            return t[i];                                                                                  \
-        }                                                                                                 \
         static bool launch(int v, const StageArgs& a, const T* qin, T* dq, T* qout);                  \
     };
 
-SBLI_VARIANT_SET(double, 1, SBLI_VARIANTS_D1)
-SBLI_VARIANT_SET(double, 2, SBLI_VARIANTS_D2)
-SBLI_VARIANT_SET(double, 3, SBLI_VARIANTS_D3)
-SBLI_VARIANT_SET(double, 4, SBLI_VARIANTS_D4)
-SBLI_VARIANT_SET(float, 1, SBLI_VARIANTS_F1)
-SBLI_VARIANT_SET(float, 2, SBLI_VARIANTS_F2)
-SBLI_VARIANT_SET(float, 3, SBLI_VARIANTS_F3)
-SBLI_VARIANT_SET(float, 4, SBLI_VARIANTS_F4)
+SBLI_VARIANT_SET(double, 1)
+SBLI_VARIANT_SET(double, 2)
+SBLI_VARIANT_SET(double, 3)
+SBLI_VARIANT_SET(double, 4)
+SBLI_VARIANT_SET(float, 1)
+SBLI_VARIANT_SET(float, 2)
+SBLI_VARIANT_SET(float, 3)
+SBLI_VARIANT_SET(float, 4)
 
 #if defined(SBLI_STAGE_TU_TYPE) && defined(SBLI_STAGE_TU_R) && defined(SBLI_STAGE_TU_LIST)
 bool VariantSet<SBLI_STAGE_TU_TYPE, SBLI_STAGE_TU_R>::launch(int v, const StageArgs& a, const T* qin, T* dq,
@@ -118,35 +82,16 @@ bool VariantSet<SBLI_STAGE_TU_TYPE, SBLI_STAGE_TU_R>::launch(int v, const StageA
 #endif
 
 #undef SBLI_TRY
-#undef SBLI_ENTRY
 #undef SBLI_VARIANT_SET
 
 // Runtime dispatch over (radius, variant) for one element type.
 template <typename T>
 struct StageDispatch {
-    static int count(int r);
-    static StageVariant get(int r, int i);
+    static int count(int r) { return fused_variants(sizeof(T) == 8 ? SBLI_F64 : SBLI_F32, r).n; }
+    static StageVariant get(int r, int i) { return fused_variants(sizeof(T) == 8 ? SBLI_F64 : SBLI_F32, r).v[i]; }
     static bool launch(int r, int v, const StageArgs& a, const T* qin, T* dq, T* qout);
 };
 
-template <typename T>
-inline int StageDispatch<T>::count(int r) {
-    switch (r) {
-        case 1: return VariantSet<T, 1>::count();
-        case 2: return VariantSet<T, 2>::count();
-        case 3: return VariantSet<T, 3>::count();
-        default: return VariantSet<T, 4>::count();
-    }
-}
-template <typename T>
-inline StageVariant StageDispatch<T>::get(int r, int i) {
-    switch (r) {
-        case 1: return VariantSet<T, 1>::get(i);
-        case 2: return VariantSet<T, 2>::get(i);
-        case 3: return VariantSet<T, 3>::get(i);
-        default: return VariantSet<T, 4>::get(i);
-    }
-}
 template <typename T>
 inline bool StageDispatch<T>::launch(int r, int v, const StageArgs& a, const T* qin, T* dq, T* qout) {
     switch (r) {

@@ -1,0 +1,108 @@
+"""The launch rule's host arithmetic (csrc/launch_rule.h), compiled on the CPU: both searches time
+the configuration they start from, sbli_init's choice for a grid is among what sbli_autotune times,
+and an ensemble's chunks are no longer than its cap."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include "launch_rule.h"
+using namespace sbli;
+static sbli_params cube(int n) { sbli_params p{}; p.nx = p.ny = p.nz = n; return p; }
+static int box_chunk(int n, int chunk) {   // as the ensemble's table splits a box
+    const int c = chunk < n ? chunk : n, k = (n + c - 1) / c;
+    return (n + k - 1) / k;
+}
+int main() {
+    int bad = 0;
+    Launch cand[kMaxTried];
+    for (int dtype : {SBLI_F64, SBLI_F32})
+        for (int r = 1; r <= 4; ++r) {
+            const int nv = fused_variants(dtype, r).n;
+            for (int n = 4 * r + 1; n <= 520; n += n < 260 ? 1 : 13) {
+                const sbli_params p = cube(n);
+                Launch def{-1, 0};
+                choose_fused(dtype, r, &p, 1, &def.variant, &def.zchunk);
+                if (def.variant < 0 || def.variant >= nv || def.zchunk < 1 || def.zchunk > n) { printf("default %d %d %d\n", dtype, r, n); ++bad; }
+                // from another configuration, and from the staged form, the rule's own is still timed
+                for (Launch entry : {def, Launch{0, n}, Launch{nv - 1, 1}, Launch{nv, n}}) {
+                    const int nc = tuning_candidates(dtype, r, &p, entry, cand);
+                    bool has = false, from = entry.variant == nv || (cand[0].variant == entry.variant && cand[0].zchunk == entry.zchunk);
+                    for (int k = 0; k < nc; ++k) {
+                        has |= cand[k].variant == def.variant && cand[k].zchunk == def.zchunk;
+                        if (cand[k].variant < 0 || cand[k].variant >= nv || cand[k].zchunk < 1 || cand[k].zchunk > n) ++bad;
+                    }
+                    if (!has || !from || nc >= kMaxTried) { printf("single %d %d %d\n", dtype, r, n); ++bad; }
+                }
+            }
+            for (int count : {1, 2, 3, 5, 8, 16, 40, 64})
+                for (int n = 4 * r + 1; n <= 128; n += 5) {
+                    sbli_params p[64];
+                    for (int i = 0; i < count; ++i) p[i] = cube(i % 3 == 1 ? (n + 4 * r + 1) / 2 + 4 * r : n);
+                    Launch start{-1, 0};
+                    choose_fused(dtype, r, p, count, &start.variant, &start.zchunk);
+                    for (Launch entry : {start, Launch{0, 7}, Launch{nv - 1, 128}}) {
+                        const int ze = capped_chunk(dtype, r, entry.variant, p, count, entry.zchunk);
+                        if (ze < 1 || ze > entry.zchunk) { printf("cap %d %d %d %d\n", dtype, r, count, n); ++bad; }
+                        const int nc = batch_candidates(dtype, r, p, count, entry, cand);
+                        bool timed = false;
+                        for (int k = 0; k < nc && !timed; ++k) {
+                            if (cand[k].variant != entry.variant) continue;
+                            const int zk = capped_chunk(dtype, r, cand[k].variant, p, count, cand[k].zchunk);
+                            timed = true;
+                            for (int i = 0; i < count; ++i) timed &= box_chunk(p[i].nz, zk) == box_chunk(p[i].nz, ze);
+                        }
+                        if (!timed || nc >= kMaxTried) { printf("batch %d %d %d %d\n", dtype, r, count, n); ++bad; }
+                    }
+                }
+        }
+    printf("%d\n", bad);
+    return bad != 0;
+}
+"""
+
+
+def test_searches_time_what_they_start_from(tmp_path):
+    src = tmp_path / "rule.cpp"
+    src.write_text(PROGRAM)
+    exe = tmp_path / "rule"
+    csrc = os.path.join(ROOT, "paper_1609_01277_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", csrc, "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout[-2000:]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,n,count", [("f32", 32, 2), ("f32", 48, 2), ("f64", 32, 4), ("f32", 32, 8)])
+def test_tuned_small_ensemble_is_not_slower(dtype, n, count):
+    """Chunks of 16 planes and more leave most of the chip idle here: by the launch model 1.6 to 2.7
+    times the untuned configuration's time, which the search therefore must not end on."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU test run without a HIP device")
+    import paper_1609_01277_amd as sbli
+    import synth
+    b = sbli.Batch(synth.batch_instances(count=count, seed=2, sizes=(n,)), order=4, dtype=dtype)
+    q, qt, dq = b.tgv_init(b.empty_state()), b.empty_state(), b.empty_state()
+
+    def us():
+        b.step(q, qt, dq, 10)
+        best = 1e9
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            b.step(q, qt, dq, 50)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 1000 / 150)
+        return best
+
+    before = us()
+    b.autotune(reps=5)
+    after = us()
+    print(dtype, n, count, "us a stage untuned %.1f tuned %.1f" % (before, after), b.get_tuning(), flush=True)
+    assert after <= 1.25 * before
