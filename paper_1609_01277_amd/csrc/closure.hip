@@ -51,7 +51,7 @@ struct sbli_net {
     int wgrad_wg = kWgradWg;
     double* loss_part = nullptr;
     double* loss = nullptr;
-    unsigned* guard_state = nullptr; // [2], zero between guard calls (see closure_guard_kernel)
+    unsigned* guard_state = nullptr; // zero between guard calls (see closure_guard_kernel)
     int conservative = 0;            // remove each output field's box mean in sbli_net_forward
     double* mean_part = nullptr;     // box-mean partial sums [max_batch * 5][chunks]
     float* mean_val = nullptr;       // box means [max_batch * 5]
@@ -159,7 +159,7 @@ extern "C" int sbli_net_create(int n, int max_batch, void* hip_stream, sbli_net*
     alloc((void**)&net->bpart, sizeof(float) * (size_t)kBiasWg * 32);
     alloc((void**)&net->loss_part, sizeof(double) * nblk(NP));
     alloc((void**)&net->loss, sizeof(double));
-    alloc((void**)&net->guard_state, 2 * sizeof(unsigned));
+    alloc((void**)&net->guard_state, sizeof(unsigned));
     alloc((void**)&net->mean_part, sizeof(double) * (size_t)max_batch * 5 * nblk(net->P, kBoxMeanChunk));
     alloc((void**)&net->mean_val, sizeof(float) * (size_t)max_batch * 5);
     if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
@@ -406,8 +406,18 @@ extern "C" int sbli_net_train_step(sbli_net* net, const float* q, const float* t
 
 extern "C" int sbli_net_guard(sbli_net* net, const float* c, int* flag, unsigned* counters) {
     if (!net || !c || !flag || !counters) return nfail(net, SBLI_ERR_ARG, "sbli_net_guard: NULL argument");
-    closure_guard_kernel<<<nblk(5 * net->P, kGuardPer), 256, 0, net->stream>>>(c, net->P, net->stats + 20,
-                                                                              net->guard_state, flag, counters);
+    // Calls on the net's stream follow each other and share its state word.  Graphs recorded
+    // from it can be replayed beside each other: a recorded call keeps its state in its flag.
+    unsigned* state = net->guard_state;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(net->stream, &status) != hipSuccess) {
+        (void)hipGetLastError();   // the default stream while another one captures: not recorded
+    } else if (status == hipStreamCaptureStatusActive) {
+        guard_clear_kernel<<<1, 1, 0, net->stream>>>(flag);
+        state = (unsigned*)flag;
+    }
+    closure_guard_kernel<<<nblk(5 * net->P, kGuardPer), 256, 0, net->stream>>>(c, net->P, net->stats + 20, state, flag,
+                                                                              counters);
     NHIP_TRY(net, hipGetLastError());
     return SBLI_OK;
 }

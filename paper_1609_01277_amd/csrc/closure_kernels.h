@@ -808,14 +808,17 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restri
 // +-limit[f] for its field, else 0; counters[0|1] count accepted / rejected.
 // The check reads 5 P values, 5.2 MB at 64^3: the time is that of one pass of
 // loads, so it wants many of them in flight on every CU.  A workgroup checks
-// kGuardPer values; the last one to finish (a ticket counter) writes the verdict
-// and clears `state` for the next call.  At 64^3 one workgroup of 1,024 threads
-// took 368 us, 320 workgroups of 4,096 values take about 8 us.
-// state: {values out of bounds seen, workgroups done}, both 0 before the call.
-constexpr int kGuardPer = 4096;   // divides P (a multiple of 32^3)
+// kGuardPer values; the last one to finish (a ticket counter) writes the verdict.
+// At 64^3 one workgroup of 1,024 threads took 368 us, 320 workgroups of 4,096 values
+// take about 8 us.
+// state: workgroups done, and kGuardBad once one has seen a value out of bounds; 0 before
+// the call and cleared by it.  It may be the word of `flag` itself, then cleared before.
+constexpr int kGuardPer = 4096;   // divides P (a multiple of 32^3); at most 5 * 2^18 workgroups
+constexpr unsigned kGuardBad = 1u << 30;
+__global__ void guard_clear_kernel(int* __restrict__ flag) { flag[0] = 0; }
 __global__ void __launch_bounds__(256) closure_guard_kernel(const float* __restrict__ C, int64_t P,
                                                             const float* __restrict__ limit,
-                                                            unsigned* __restrict__ state, int* __restrict__ flag,
+                                                            unsigned* state, int* flag,
                                                             unsigned* __restrict__ counters) {
     const float* src = C + (int64_t)blockIdx.x * kGuardPer + threadIdx.x;
     const float L = limit[(int64_t)blockIdx.x * kGuardPer / P];   // kGuardPer divides P: one field per workgroup
@@ -824,14 +827,13 @@ __global__ void __launch_bounds__(256) closure_guard_kernel(const float* __restr
     for (int k = 0; k < kGuardPer / 256; ++k) bad |= !(fabsf(src[256 * k]) <= L);
     const int any = __syncthreads_or(bad);
     if (threadIdx.x != 0) return;
-    if (any) atomicOr(&state[0], 1u);
-    __threadfence();
-    if (atomicAdd(&state[1], 1u) != gridDim.x - 1) return;
-    // every other workgroup's verdict was published before its ticket
-    __threadfence();
-    const unsigned rejected = atomicExch(&state[0], 0u);
-    atomicExch(&state[1], 0u);
-    flag[0] = rejected ? 0 : 1;
+    // one word, so a workgroup's verdict is there before its ticket
+    if (any) atomicOr(state, kGuardBad);
+    const unsigned seen = atomicAdd(state, 1u);
+    if ((seen & ~kGuardBad) != gridDim.x - 1) return;
+    const bool rejected = (seen & kGuardBad) != 0;
+    atomicExch(state, 0u);
+    atomicExch((unsigned*)flag, rejected ? 0u : 1u);
     atomicAdd(&counters[rejected ? 1 : 0], 1u);
 }
 
