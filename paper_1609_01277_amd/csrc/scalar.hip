@@ -343,7 +343,7 @@ constexpr int kCus = 256;
 // beyond one a CU queue, those of small buffers partly beside each other.  Measured from
 // 48^2 to 1500^2 at orders 2 to 12: its choice is the fastest of the fifteen or within
 // 15 % of it, which the other choices miss by up to 3 times.
-Route plane_tiles(const ScalarConst& c, int ax, int ay) {
+Route plane_tiles(const ScalarConst& c, int ax, int ay, int nsteps, double* us_step) {
     static const struct { int x, y; double share; } bufs[] = {{64, 64, 1.0}, {64, 48, 1.0}, {48, 48, 1.0},
                                                               {64, 32, 0.85}, {32, 32, 0.75}};
     Route best{kPerStage, ax, ay, 1, 0, 0};
@@ -351,7 +351,7 @@ Route plane_tiles(const ScalarConst& c, int ax, int ay) {
     for (const auto& b : bufs)
         for (int steps : {1, 2, 4}) {
             const int tx = b.x - 6 * c.r * steps, ty = b.y - 6 * c.r * steps;
-            if (tx < 4 || ty < 4) continue;
+            if (tx < 4 || ty < 4 || steps > std::max(nsteps, 1)) continue;
             const double gx = std::ceil((double)c.n[ax] / tx), gy = std::ceil((double)c.n[ay] / ty);
             if (gx > 65535.0 || gy > 65535.0) continue;
             const double step_us = 0.7 + b.x * b.y * (2.2 + 0.6 * c.r) / kPlanePoints;
@@ -361,7 +361,16 @@ Route plane_tiles(const ScalarConst& c, int ax, int ay) {
                 best_us = us;
             }
         }
+    *us_step = best_us;
     return best;
+}
+
+// Modelled us a step of a launch a stage on two axes: three launches and, per point, the
+// loads of the stencil.  Within 25 % of the measurements (1,024 x 1,024 to 8,192 x 8,192,
+// 12 x 2^20, 2^20 x 12, 20 x 10^5, 65,536 x 64; orders 2 to 12).
+double stage_model(const ScalarConst& c, int ax) {
+    const double ps = (c.n[ax] < 64 ? 11.0 : 17.0) + 7.0 * c.r + (c.P > (1 << 23) ? 5.0 : 0.0);
+    return 10.0 + c.P * ps * 1e-6;
 }
 
 // Measured, us a step.  One axis: a ring of 512 points 0.98 to 1.24 (orders 2 to 12),
@@ -369,9 +378,12 @@ Route plane_tiles(const ScalarConst& c, int ax, int ay) {
 // free (1000 points, order 8: 1.09 with T = 192, 1.26 with 320), and 320 points beyond
 // (200,000 points: 1.96 with 320, 2.11 with 192).  Two axes: a ring of 48^2 points 2.5
 // to 6.2, tiles 2.4 to 7.9; of 64^2 4.0 to 10.9, tiles 2.5 to 8.1.  A launch a stage
-// (8 to 134) stays for three axes and for a stencil wider than the axis, whose ghost
-// cells would hold a point more than once.
-Route choose_route(const ScalarConst& c) {
+// (8 to 134) stays for three axes, for a stencil wider than the axis, whose ghost
+// cells would hold a point more than once, and for thin grids at high orders, whose tiles
+// are mostly margin (12 x 2^20, a launch a stage and tiles: order 2 330, 413; order 12 755,
+// 1,497; 20 x 10^5: order 4 61, 58; order 8 88, 96; 65,536 x 64, order 12: 223, 299): where
+// the modelled times say so.
+Route choose_route(const ScalarConst& c, int nsteps) {
     int act[3], na = 0;
     for (int d = 0; d < 3; ++d)
         if (c.active[d]) {
@@ -385,7 +397,10 @@ Route choose_route(const ScalarConst& c) {
     }
     if (na == 2) {
         if (c.P <= kRing2Points) return {kRing2, act[0], act[1], kRingSteps, 0, 0};
-        return plane_tiles(c, act[0], act[1]);
+        double us;
+        const Route tiles = plane_tiles(c, act[0], act[1], nsteps, &us);
+        if (tiles.kind == kPerStage || stage_model(c, act[0]) < 1.05 * us) return {kPerStage, 0, 0, 1, 0, 0};
+        return tiles;
     }
     return {kPerStage, 0, 0, 1, 0, 0};
 }
@@ -454,7 +469,7 @@ extern "C" int sbli_scalar_rk3(const sbli_scalar_params* p, double* phi, double*
     const unsigned blocks = (unsigned)((c.P + 255) / 256);
     double* src = phi;
     double* dst = phi_tmp;
-    const Route route = choose_route(c);
+    const Route route = choose_route(c, nsteps);
     for (int st = 0; st < nsteps;) {
         if (route.kind != kPerStage) {
             const int k = std::min(nsteps - st, route.steps);
