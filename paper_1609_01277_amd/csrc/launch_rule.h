@@ -82,7 +82,7 @@ struct LaunchCand {
 };
 
 inline const LaunchCand* launch_cands(int dtype, int r, int& n) {
-    static const LaunchCand d1[] = {{3, 1.2, 0.8}, {2, 1.6, 0.8}}, d2[] = {{8, 1.35, 0.75}, {7, 1.7, 1.0}},
+    static const LaunchCand d1[] = {{3, 1.2, 0.8}, {2, 1.6, 1.0}}, d2[] = {{8, 1.35, 0.75}, {7, 1.7, 1.0}},
                             d3[] = {{1, 2.0, 1.0}}, d4[] = {{4, 2.4, 1.0}}, f1[] = {{3, 0.9, 0.8}, {2, 1.2, 0.8}},
                             f2[] = {{11, 1.4, 1.0}, {10, 1.95, 1.0}}, f3[] = {{3, 1.5, 1.0}}, f4[] = {{2, 1.9, 0.35}};
     const bool d = dtype == SBLI_F64;

@@ -66,14 +66,38 @@ int main() {
 """
 
 
-def test_searches_time_what_they_start_from(tmp_path):
+def _run(tmp_path, program):
     src = tmp_path / "rule.cpp"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     exe = tmp_path / "rule"
     csrc = os.path.join(ROOT, "paper_1609_01277_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", csrc, "-o", str(exe), str(src)], check=True)
-    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    return subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+
+
+def test_searches_time_what_they_start_from(tmp_path):
+    out = _run(tmp_path, PROGRAM)
     assert out.returncode == 0, out.stdout[-2000:]
+
+
+def test_order_2_chunks_fill_one_round(tmp_path):
+    """FP64 order 2 in 32 x 8 tiles, one workgroup a CU: a second round costs as much as the first
+    (128^3 in chunks of 16 planes 100 us a stage, of 32 planes 90; 256^3 of 64: 676, of 256: 644)."""
+    out = _run(tmp_path, r"""
+#include <cstdio>
+#include "launch_rule.h"
+using namespace sbli;
+int main() {
+    for (const int* n : {(const int[]){128, 128, 128}, (const int[]){256, 256, 256}, (const int[]){400, 64, 64}}) {
+        sbli_params p{};
+        p.nx = n[0], p.ny = n[1], p.nz = n[2];
+        int v = -1, zc = 0;
+        choose_fused(SBLI_F64, 1, &p, 1, &v, &zc);
+        printf("%d %d\n", v, zc);
+    }
+}
+""")
+    assert out.stdout.split() == ["2", "32", "2", "256", "2", "32"]
 
 
 @pytest.mark.gpu
