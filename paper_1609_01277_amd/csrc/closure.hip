@@ -427,8 +427,16 @@ extern "C" int sbli_net_n(const sbli_net* net) { return net ? net->n : SBLI_ERR_
 extern "C" void* sbli_net_stream(const sbli_net* net) { return net ? (void*)net->stream : nullptr; }
 
 // The row form where its 16-byte loads are aligned (rows are whole multiples of
-// `ratio` values, so the base decides, except for two FP32 values a load) and the grid
-// fits its launch; every other ratio, alignment and size takes the pointwise form.
+// `ratio` values, so the base decides, except for two FP32 values a load), the grid fits
+// its launch and short rows do not waste it: a wavefront takes a row of up to 64 outputs,
+// and once many fields fill the chip the idle lanes of a short one count.  320 fields, us
+// pointwise and by rows: ratio 2, 16 outputs a row 32 and 43, 20 outputs 61 and 61; ratio 4
+// 8 outputs 33 and 51, 12 outputs 136 and 146 (FP32: 10 outputs 45 and 64, 12 outputs 96
+// and 75); ratio 8, 8 outputs 330 and
+// 460 (FP32 286 and 222; 6 outputs 152 and 165).  On a chip with room (5 fields) rows take
+// a half to a quarter of the pointwise time at ratios 4 and 8 however short they are, and
+// at ratio 2 the two take the same.  Every other ratio, alignment and size takes the
+// pointwise form.
 template <typename Tin>
 static void box_filter_launch(hipStream_t s, const Tin* fine, int nf, int nfields, int ratio, float* coarse,
                               int subtract) {
@@ -442,7 +450,9 @@ static void box_filter_launch(hipStream_t s, const Tin* fine, int nf, int nfield
     while (zper > 1 && across * ((nc + zper - 1) / zper) < 5 * 256) zper /= 2;
     const int64_t gz = (int64_t)nfields * ((nc + zper - 1) / zper);
     const dim3 grid((nc + 63) / 64, (nc + kFilterWaves - 1) / kFilterWaves, (unsigned)gz);
-    const bool rows = (uintptr_t)fine % 16 == 0 && grid.y <= 65535 && gz <= 65535;
+    const bool full = across * ((nc + kFilterZ - 1) / kFilterZ) >= 5 * 256;
+    const int shortest = ratio == 2 ? 20 : !full ? 1 : ratio == 4 ? (sizeof(Tin) == 8 ? 14 : 12) : sizeof(Tin) == 8 ? 12 : 7;
+    const bool rows = (uintptr_t)fine % 16 == 0 && grid.y <= 65535 && gz <= 65535 && nc >= shortest;
     if (rows && ratio == 2)
         box_filter_rows_kernel<Tin, 2><<<grid, 64 * kFilterWaves, 0, s>>>(fine, nf, coarse, subtract, zper);
     else if (rows && ratio == 4)
