@@ -295,12 +295,14 @@ enum { kEpiGelu = 0, kEpiLinear = 1, kEpiDGelu = 2, kEpiData = 3 };
 // step ahead.  4 x 64^3 points, 32 -> 32 channels with GELU: 145 -> 109 us (201 MB of
 // outputs take 44, the MFMAs 27), 32 -> 5: 100 -> 69, backward data 32 -> 32: 147 -> 125;
 // 8 -> 32: 62 -> 53.  The 8-channel forms have 14 steps and more workgroups a CU; there
-// requests ahead cost registers (backward data 81 -> 103 us) and are left out.
+// requests ahead cost registers (backward data 81 -> 103 us) and are left out, and the
+// backward-data form with weights by rows, which holds its 32 pre-activations, takes two
+// wavefronts a SIMD (with three it spills: 57 -> 62 us).
 constexpr int kConvTx = 32, kConvTy = 8;
 constexpr int kConvHx = kConvTx + 2, kConvHy = kConvTy + 2;
 
 template <int EPI, int CPAD, bool FRAG>
-__global__ void __launch_bounds__(256, CPAD == 8 ? 3 : 2) conv_mfma_lds_kernel(const __bf16* __restrict__ in, const __bf16* __restrict__ Wp,
+__global__ void __launch_bounds__(256, CPAD == 8 && (FRAG || EPI != kEpiDGelu) ? 3 : 2) conv_mfma_lds_kernel(const __bf16* __restrict__ in, const __bf16* __restrict__ Wp,
                                                             int Kpad, const float* __restrict__ bias, int n,
                                                             float* __restrict__ fout, __bf16* __restrict__ bout,
                                                             const float* __restrict__ pre_in, int ocount, int ostride) {
@@ -362,12 +364,16 @@ __global__ void __launch_bounds__(256, CPAD == 8 ? 3 : 2) conv_mfma_lds_kernel(c
     __syncthreads();
     floatx16 acc0 = {0}, acc1 = {0};
     const int ry0 = 2 * wave;                             // tile rows ry0, ry0 + 1 of the two M tiles
-    // this lane's element in the box row ry0 by dx and channel group, each tap a constant from there
-    const __bf16* lx[3][CPAD == 32 ? 2 : 1];
+    // this lane's element in the box row ry0 (CPAD = 32: by dx and channel group), each tap a
+    // constant from there.  (Elements, not pointers: a choice between two pointers loses that they
+    // point to LDS, and its reads become flat loads, which cost the 8-channel forms a third of
+    // their time.)
+    const int lx8 = at(ry0, row, 0);
+    int lx[3][2];
 #pragma unroll
     for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-        for (int c = 0; c < (CPAD == 32 ? 2 : 1); ++c) lx[dx][c] = &sx[at(ry0, row + dx, CPAD == 32 ? 2 * c + half : 0)];
+        for (int c = 0; c < 2; ++c) lx[dx][c] = at(ry0, row + dx, 2 * c + half);
     constexpr int RS = kConvHx * CPAD;                    // from a box row to the next
     auto row_off = [](int t) { return ((t / 9) * kConvHy + (t / 3) % 3) * RS; };
     // The K loop runs over the packed width round_up(27 * CPAD, 16) (the value of
@@ -393,16 +399,16 @@ __global__ void __launch_bounds__(256, CPAD == 8 ? 3 : 2) conv_mfma_lds_kernel(c
     // Operands are requested ahead, weights kAheadW steps (L2 latency), points one step (LDS).
     auto points = [&](int k0, bf16x8& a0, bf16x8& a1) {
         if (CPAD == 32 || k0 / CPAD + half < 27) {
-            const __bf16* a;
+            int a;
             if constexpr (CPAD == 32) {
                 const int t = k0 / 32;
                 a = lx[t % 3][k0 % 32 / 16] + row_off(t);
             } else {
                 const int t = k0 / CPAD;
-                a = half ? lx[(t + 1) % 3][0] + row_off(t + 1) : lx[t % 3][0] + row_off(t);
+                a = lx8 + (half ? row_off(t + 1) + (t + 1) % 3 * CPAD : row_off(t) + t % 3 * CPAD);
             }
-            a0 = *(const bf16x8*)a;
-            a1 = *(const bf16x8*)(a + RS);                // next row
+            a0 = *(const bf16x8*)&sx[a];
+            a1 = *(const bf16x8*)&sx[a + RS];             // next row
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j) { a0[j] = (__bf16)0.0f; a1[j] = (__bf16)0.0f; }
