@@ -162,6 +162,43 @@ inline int capped_chunk(int dtype, int r, int v, const sbli_params* p, int count
 struct Launch {
     int variant, zchunk;
 };
+
+// What a search keeps.  A later candidate replaces the best one only when it is faster by more
+// than 1 %: candidates within timing noise of each other then resolve to the same (earlier)
+// choice on every run.  The configuration in use comes first, before the clocks are up (64
+// FP32 boxes: 2.97 ms a step for what then takes 2.67), and a launch timed after a slow variant
+// reads 2 to 3 % high.  So a winner and the configuration in use are timed in turn at the end,
+// twice each, and the latter is left only for one that is 1 % faster there.  Without this the
+// search over those boxes left caps of 48 planes for 128, equal over the two steps it times:
+// 26.1 instead of 25.5 ms for ten steps together, and 305 instead of 192 box by box, where
+// long chunks leave most of the chip idle.
+constexpr float kTuneMargin = 0.99f;
+constexpr int kTuneTurns = 4;   // the winner first, whose own predecessor may be a slow one
+struct TuneBest {
+    Launch start, at;      // the configuration in use, and the best so far
+    float ms = 1e30f, ms_start = 1e30f, ms_at = 1e30f;
+    bool moved = false;    // at is another one than start
+    explicit TuneBest(Launch s) : start(s), at(s) {}
+    void offer(Launch c, float t, bool first) {
+        if (t < ms * kTuneMargin) {
+            at = c;
+            ms = t;
+            moved = !first;
+        }
+    }
+    int turns() const { return moved ? kTuneTurns : 0; }
+    Launch turn(int k) const { return k & 1 ? start : at; }
+    void turned(int k, float t) {
+        float& m = k & 1 ? ms_start : ms_at;
+        m = std::min(m, t);
+    }
+    void settle() {   // without turns, or where one could not be launched, `at` stays
+        if (ms_start == 1e30f || ms_at == 1e30f) return;
+        moved = ms_at < ms_start * kTuneMargin;
+        ms = moved ? ms_at : ms_start;
+        if (!moved) at = start;
+    }
+};
 constexpr int kMaxTried = 256;
 
 // What sbli_autotune times of the fused form, in order: the configuration in use (unless it
@@ -189,23 +226,28 @@ inline int tuning_candidates(int dtype, int r, const sbli_params* p, Launch entr
     return n;
 }
 
-// What sbli_batch_autotune times, in order: each variant under caps of 128 to 16 planes, then
-// the configuration in use; one that launches like an earlier one is left out.
+// What sbli_batch_autotune times, in order: the configuration in use (as a cap of the list
+// below where one launches alike), then each variant under caps of 128 to 16 planes; one that
+// launches like an earlier one is left out.
 inline int batch_candidates(int dtype, int r, const sbli_params* p, int count, Launch entry, Launch* out) {
     const VariantList l = fused_variants(dtype, r);
     int nmax = 1, n = 0, chunk[kMaxTried];
     for (int i = 0; i < count; ++i) nmax = std::max(nmax, p[i].nz);
+    auto planes = [&](int v, int zmax) { return std::min(capped_chunk(dtype, r, v, p, count, zmax), nmax); };
     auto add = [&](int v, int zmax) {
-        const int zc = std::min(capped_chunk(dtype, r, v, p, count, zmax), nmax);
+        const int zc = planes(v, zmax);
         for (int k = 0; k < n; ++k)
             if (out[k].variant == v && chunk[k] == zc) return;
         if (n == kMaxTried) return;
         chunk[n] = zc;
         out[n++] = {v, zmax};
     };
-    for (int v = 0; v < l.n; ++v)
-        for (int zmax : {128, 96, 64, 48, 32, 16}) add(v, zmax);
+    constexpr int caps[] = {128, 96, 64, 48, 32, 16};
+    for (int zmax : caps)
+        if (n == 0 && planes(entry.variant, zmax) == planes(entry.variant, entry.zchunk)) add(entry.variant, zmax);
     add(entry.variant, entry.zchunk);
+    for (int v = 0; v < l.n; ++v)
+        for (int zmax : caps) add(v, zmax);
     return n;
 }
 

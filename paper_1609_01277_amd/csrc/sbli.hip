@@ -539,10 +539,6 @@ extern "C" int sbli_get_tuning(const sbli_ctx* ctx, int* variant, int* zchunk) {
     return SBLI_OK;
 }
 
-// A later candidate replaces the best one only when it is faster by more than 1 %: candidates
-// within timing noise of each other then resolve to the same (earlier) choice on every run.
-constexpr float kTuneMargin = 0.99f;
-
 extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, double dt, int reps, double* best_ms) {
     if (!ctx) return fail(nullptr, SBLI_ERR_ARG, "sbli_autotune: ctx is NULL");
     if (!q || !q_tmp || !dq) return fail(ctx, SBLI_ERR_ARG, "sbli_autotune: NULL state pointer");
@@ -550,8 +546,8 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
     const size_t bytes = 5 * (size_t)npoints(ctx) * elem_size(ctx);
     if (overlaps(q, q_tmp, bytes) || overlaps(q, dq, bytes) || overlaps(q_tmp, dq, bytes))
         return fail(ctx, SBLI_ERR_ARG, "sbli_autotune: q, q_tmp and dq must not overlap");
-    // The configuration in use is timed first, so the search cannot end on a slower one; the
-    // staged form is skipped when its scratch cannot be allocated.
+    // The configuration in use is timed first and against the winner (TuneBest); the staged
+    // form is skipped when its scratch cannot be allocated.
     const Launch entry{ctx->variant, ctx->zchunk}, staged{num_fused(ctx), ctx->p.nz};
     Launch cands[kMaxTried + 1];
     int nc = 0;
@@ -561,13 +557,13 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
     hipEvent_t e0, e1;
     HIP_TRY(ctx, hipEventCreate(&e0));
     HIP_TRY(ctx, hipEventCreate(&e1));
-    float best = 1e30f;
-    int bv = ctx->variant, bz = ctx->zchunk;
+    TuneBest best(entry);
     const bool old_rule = ctx->by_rule;
     ctx->by_rule = false;
-    for (int ci = 0; ci < nc; ++ci) {
-        ctx->variant = cands[ci].variant;
-        ctx->zchunk = cands[ci].zchunk;
+    for (int ci = 0; ci < nc + (ci < nc ? 0 : best.turns()); ++ci) {
+        const Launch cand = ci < nc ? cands[ci] : best.turn(ci - nc);
+        ctx->variant = cand.variant;
+        ctx->zchunk = cand.zchunk;
         if (update_table(ctx) != hipSuccess) {
             (void)hipGetLastError();
             continue;
@@ -584,25 +580,23 @@ extern "C" int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, doub
             // cleanup after the failure reported below
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
-            ctx->variant = bv;
-            ctx->zchunk = bz;
-            ctx->by_rule = old_rule && best == 1e30f;
+            ctx->variant = best.at.variant;
+            ctx->zchunk = best.at.zchunk;
+            ctx->by_rule = old_rule && best.ms == 1e30f;
             (void)update_table(ctx);
             if (rc != SBLI_OK) return rc;
             return fail(ctx, SBLI_ERR_HIP, "sbli_autotune: %s", hipGetErrorString(err));
         }
-        if (ms < best * kTuneMargin) {
-            best = ms;
-            bv = cands[ci].variant;
-            bz = cands[ci].zchunk;
-        }
+        if (ci < nc) best.offer(cand, ms, ci == 0);
+        else best.turned(ci - nc, ms);
     }
+    best.settle();
     const hipError_t d0 = hipEventDestroy(e0), d1 = hipEventDestroy(e1);
-    ctx->variant = bv;
-    ctx->zchunk = bz;
+    ctx->variant = best.at.variant;
+    ctx->zchunk = best.at.zchunk;
     HIP_TRY(ctx, update_table(ctx));
     HIP_TRY(ctx, d0 != hipSuccess ? d0 : d1);
-    if (best_ms) *best_ms = best / reps;
+    if (best_ms) *best_ms = best.ms / reps;
     return SBLI_OK;
 }
 
@@ -941,13 +935,13 @@ extern "C" int sbli_batch_autotune(sbli_batch* b, void* q, void* q_tmp, void* dq
     hipEvent_t e0, e1;
     BHIP_TRY(b, hipEventCreate(&e0));
     BHIP_TRY(b, hipEventCreate(&e1));
-    float best = 1e30f;
-    int bv = b->variant, bz = b->zmax;
+    TuneBest best(cands[0]);   // which launches as the configuration in use
     hipError_t err = hipSuccess;
     // a failure ends the loop; rc and err then hold it
-    for (int ci = 0; ci < nc; ++ci) {
-        b->variant = cands[ci].variant;
-        b->zmax = cands[ci].zchunk;
+    for (int ci = 0; ci < nc + (ci < nc ? 0 : best.turns()); ++ci) {
+        const Launch cand = ci < nc ? cands[ci] : best.turn(ci - nc);
+        b->variant = cand.variant;
+        b->zmax = cand.zchunk;
         rc = batch_build_table(b);
         if (rc != SBLI_OK) break;
         batch_enqueue(b, b->stream, q, q_tmp, dq, 1);
@@ -962,21 +956,19 @@ extern "C" int sbli_batch_autotune(sbli_batch* b, void* q, void* q_tmp, void* dq
         float ms = 0.f;
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         if (err != hipSuccess) break;
-        if (ms < best * kTuneMargin) {
-            best = ms;
-            bv = cands[ci].variant;
-            bz = cands[ci].zchunk;
-        }
+        if (ci < nc) best.offer(cand, ms, ci == 0);
+        else best.turned(ci - nc, ms);
     }
+    best.settle();
     const hipError_t d0 = hipEventDestroy(e0), d1 = hipEventDestroy(e1);
     if (err == hipSuccess) err = d0 != hipSuccess ? d0 : d1;
-    b->variant = bv;
-    b->zmax = bz;
+    b->variant = best.at.variant;
+    b->zmax = best.at.zchunk;
     const int rc2 = batch_build_table(b);
     if (rc != SBLI_OK) return rc;   // batch_build_table has recorded the message
     if (err != hipSuccess) return bfail(b, SBLI_ERR_HIP, "sbli_batch_autotune: %s", hipGetErrorString(err));
     if (rc2 != SBLI_OK) return rc2;
-    if (best_ms) *best_ms = best / reps;
+    if (best_ms) *best_ms = best.ms / reps;
     return SBLI_OK;
 }
 

@@ -80,6 +80,79 @@ def test_searches_time_what_they_start_from(tmp_path):
     assert out.returncode == 0, out.stdout[-2000:]
 
 
+def test_batch_search_times_its_start_first(tmp_path):
+    """A later candidate has to be 1 % faster than the best so far: with the configuration in use
+    behind the others, near ties went against it (64 FP32 boxes of 32 to 128 points: caps of 128
+    planes for its 48, and box-by-box steps of 30.5 ms for 19.2)."""
+    out = _run(tmp_path, r"""
+#include <cstdio>
+#include "launch_rule.h"
+using namespace sbli;
+int main() {
+    int bad = 0;
+    Launch cand[kMaxTried];
+    for (int dtype : {SBLI_F64, SBLI_F32})
+        for (int r = 1; r <= 4; ++r) {
+            const int nv = fused_variants(dtype, r).n;
+            for (int count : {1, 2, 3, 5, 8, 16, 40, 64})
+                for (int n = 4 * r + 1; n <= 128; n += 5) {
+                    sbli_params p[64] = {};
+                    int nmax = 0;
+                    for (int i = 0; i < count; ++i) {
+                        p[i].nx = p[i].ny = p[i].nz = i % 3 == 1 ? (n + 4 * r + 1) / 2 + 4 * r : n;
+                        nmax = std::max(nmax, p[i].nz);
+                    }
+                    Launch start{-1, 0};
+                    choose_fused(dtype, r, p, count, &start.variant, &start.zchunk);
+                    for (Launch entry : {start, Launch{0, 7}, Launch{nv - 1, 48}, Launch{nv / 2, 500}}) {
+                        const int nc = batch_candidates(dtype, r, p, count, entry, cand);
+                        const int v = entry.variant;
+                        const int a = std::min(nmax, capped_chunk(dtype, r, v, p, count, entry.zchunk));
+                        const int b = std::min(nmax, capped_chunk(dtype, r, v, p, count, cand[0].zchunk));
+                        bad += nc < 1 || cand[0].variant != v || a != b;
+                        for (int k = 0; k < nc; ++k)   // nothing is launched alike twice
+                            for (int j = 0; j < k; ++j)
+                                bad += cand[k].variant == cand[j].variant && cand[k].zchunk == cand[j].zchunk;
+                    }
+                }
+        }
+    printf("%d\n", bad);
+}
+""")
+    assert out.stdout.split() == ["0"]
+
+
+def test_a_search_leaves_its_start_only_for_a_faster_one(tmp_path):
+    """The first timing is made with the clocks down (2.97 ms for a launch that takes 2.67) and one
+    after a slow variant reads high: near ties, timed in turn, stay with the configuration in use."""
+    out = _run(tmp_path, r"""
+#include <cstdio>
+#include "launch_rule.h"
+using namespace sbli;
+static void search(float cold, float b, float c, const float (&t)[kTuneTurns]) {
+    TuneBest s({7, 48});
+    s.offer({7, 48}, cold, true);
+    s.offer({9, 64}, b, false);
+    s.offer({7, 128}, c, false);
+    for (int k = 0; k < s.turns(); ++k) {
+        const Launch l = s.turn(k);
+        if (k & 1 ? l.variant != 7 || l.zchunk != 48 : l.variant == 7 && l.zchunk == 48) printf("turn ");
+        s.turned(k, t[k]);
+    }
+    s.settle();
+    printf("%d %d %.2f\n", s.at.variant, s.at.zchunk, s.ms);
+}
+int main() {
+    search(2.97f, 2.80f, 2.66f, {2.70f, 2.67f, 2.66f, 2.67f});   // a near tie
+    search(2.97f, 2.80f, 2.60f, {2.68f, 2.68f, 2.61f, 2.69f});   // 3 % faster
+    search(2.97f, 2.60f, 2.59f, {2.62f, 2.70f, 2.61f, 2.69f});   // two faster ones within noise: the earlier
+    search(2.69f, 2.80f, 2.75f, {1.f, 1.f, 1.f, 1.f});           // nothing faster: no turns
+    search(2.97f, 2.80f, 2.60f, {2.58f, 1e30f, 2.58f, 1e30f});   // the start could not be timed again
+}
+""")
+    assert out.stdout.split() == "7 48 2.67 7 128 2.61 9 64 2.61 7 48 2.69 7 128 2.60".split()
+
+
 def test_order_2_chunks_fill_one_round(tmp_path):
     """FP64 order 2 in 32 x 8 tiles, one workgroup a CU: a second round costs as much as the first
     (128^3 in chunks of 16 planes 100 us a stage, of 32 planes 90; 256^3 of 64: 676, of 256: 644)."""
