@@ -110,7 +110,10 @@ int sbli_tgv_init(sbli_ctx* ctx, void* q, const double* phase);
  * every stencil, the nested ones included, sees the mirror image of the state,
  * which makes the result that of the periodic box of twice the length holding
  * the state and its mirror image).  `q` and `rhs` are device states of the
- * context's dtype and must not overlap.
+ * context's dtype and must not overlap.  In FP32 the sums run in another order
+ * than inside sbli_rk3_step: the two round the same residual differently (a few
+ * parts in 1e7 of its largest terms), so steps put together from sbli_rhs are
+ * not bitwise those of sbli_rk3_step.
  */
 int sbli_rhs(sbli_ctx* ctx, const void* q, void* rhs);
 
@@ -149,8 +152,8 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  * every (dtype, order) is the staged form: two launches, one thread per point,
  * with the nested fields (6 words per point) in library-owned device memory,
  * allocated when the form is first selected and kept until sbli_destroy; orders 10 and 12
- * have only this variant.  All variants compute bitwise identical results; only speed
- * differs.  sbli_init selects a variant and a zchunk by the grid's size: the staged form
+ * have only this variant.  All variants of one call compute bitwise identical results;
+ * only speed differs.  sbli_init selects a variant and a zchunk by the grid's size: the staged form
  * for orders 6 (FP32: up to 96^3 points) and 8 while its scratch is at most 1/64 of the
  * device's free memory and that of all contexts that took it this way at most 1/64 of the
  * device's memory, else a fused variant and a zchunk that fill the device (sbli_set_tuning
@@ -161,14 +164,17 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  * beside other work of the context, another such graph included.  Where the staged form is
  * only sbli_init's choice, a captured call records the fused form instead, which has no
  * such state; sbli_set_tuning, sbli_autotune and orders 10 and 12 make it the caller's.
+ * A graph keeps the launch configuration and the attached network of its capture: record
+ * it again after sbli_set_tuning, sbli_autotune or sbli_closure_attach.
  *
  * sbli_num_variants: number of variants for the context (>= 1), or < 0 on error.
  * sbli_variant_info: info = {tile x, tile y, load-ahead depth, register-window
  *   rotation (1) or shifting (0), wavefronts per SIMD its register allocation
  *   allows at least (1: as many registers as the kernel wants), barrier
- *   schedule (0: two barriers per z-plane; 1: double-buffered LDS planes, one
- *   barrier; 2: one barrier, the work split between two kinds of wavefronts), where the R planes below the output plane are kept (0: registers,
- *   1: LDS)} of a variant (7 ints written); all seven are 0 for the staged form.
+ *   schedule (0: two barriers per z-plane; 1: one, with more buffers of the LDS
+ *   planes; 2: one, the work split between two kinds of wavefronts), where the R
+ *   planes below the output plane are kept (0: registers, 1: LDS)} of a variant
+ *   (7 ints written); all seven are 0 for the staged form.
  * sbli_set_tuning / sbli_get_tuning: select / read the variant and zchunk used
  *   by sbli_rhs and sbli_rk3_step (1 <= zchunk <= nz; the staged form ignores
  *   zchunk).  sbli_set_tuning waits for the context's stream (it updates a small
@@ -179,8 +185,9 @@ int sbli_diagnostics(sbli_ctx* ctx, const void* q, double out[7]);
  *   context's stream, `reps` RK3 steps each after one warm-up step) using the
  *   caller's device buffers, then select the fastest (a later candidate replaces
  *   the best so far only when more than 1 % faster, so near-ties resolve to the
- *   selection at the call, the earlier variant and the longer zchunk); *best_ms (may be NULL) receives the
- *   selected candidate's time per step.  The contents of q, q_tmp and dq afterwards are
+ *   earlier variant and the longer zchunk; the selection at the call is left only
+ *   for one that is 1 % faster when the two are then timed in turn); *best_ms
+ *   (may be NULL) receives the selected candidate's time per step.  The contents of q, q_tmp and dq afterwards are
  *   unspecified (they are advanced in time).  Synchronises the stream.
  */
 int sbli_num_variants(const sbli_ctx* ctx);
@@ -218,7 +225,8 @@ int sbli_autotune(sbli_ctx* ctx, void* q, void* q_tmp, void* dq, double dt, int 
  * sbli_batch_set_tuning / get_tuning / autotune: variant (as for a single box)
  *   and the cap on z-planes per workgroup (zmax); changing them drops the graph.
  *   Where workgroups of zmax planes would leave compute units idle, they take fewer.
- *   autotune times every variant with zmax 128 to 16, and the selection at the call.
+ *   autotune times the selection at the call, then every variant with zmax 128 to 16,
+ *   and leaves the former as sbli_autotune does.
  * In all calls q, q_tmp, dq are distinct device buffers of offsets[count]
  * elements; the result is in q.
  */

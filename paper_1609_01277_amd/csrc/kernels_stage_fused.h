@@ -277,7 +277,9 @@ __device__ __forceinline__ T nested_G(T t, const PF<T>& s, const BoxConst<T>& c)
 // Q, Q u, u, p, theta and V took 41 a pair and 27 a direction.  The factor -2 is exact and
 // saves a second set of weights.  RMS error against 113-bit arithmetic over that of those
 // separate sums, orders 2 to 12, both types: mass 0.76 to 0.86, momentum 0.60 to 0.81,
-// energy 0.64 to 0.70.
+// energy 0.64 to 0.70; with the bracket in the mass row, too, u = m rr and p from the internal
+// energy: 1.73 to 1.97, 1.00 to 1.02, 0.85 to 0.92.  The difference costs 3 to 4 % of a launch
+// at FP64 order 4 (512^3), 3 % at order 8, 5 to 6 % at order 12 and 1 % at FP32 order 4.
 template <typename T, bool PLAIN>
 struct ResidualSums {
     T Rr, R0, R1, R2, RE;
@@ -879,9 +881,10 @@ __device__ __forceinline__ void fused_stage_body(const T* __restrict__ q, T* __r
 // reaches 4.6) while neither VALU (34 %) nor LDS (44 %) was busy: with schedule 1 a SIMD
 // had one output wavefront, whose LDS reads, arithmetic and waits for the next plane
 // followed each other.  Per launch: 5.96 ms with the former sums and order of steps,
-// 5.43 with the sums above, x and y summed on the gradient's LDS plane and the loads a
+// 5.43 with the bracket sums, x and y summed on the gradient's LDS plane and the loads a
 // full step ahead, 4.66 in this form (bare tile alone on the chip: 2.17 -> 1.92 us a
-// plane, 2.24 in contention).  FP32, order 6, 256^3: 823 -> 614 us.  FP32 at order 4
+// plane, 2.24 in contention), 4.83 with the momentum along the axes in LDS (see
+// ResidualSums).  FP32, order 6, 256^3: 823 -> 614 us.  FP32 at order 4
 // stays with 32 x 16 tiles and schedule 1 (2.60 ms; 16 x 16 or 32 x 12 here 4.00, 2.98):
 // it is bound by VALU issue, and there the larger tile has less ring work a point.
 // One barrier a plane, as schedule 1: what is read between two barriers was written

@@ -20,7 +20,8 @@
 // r = m - rho u_2, which is at most a rounding of m and needs no more than FP32: r's own
 // rounding is 2^-24 of a unit in m's last place, so the sum rounds to m itself.
 // The residual step at 256^3, FP64, order 8: 1,231 -> 880 us, 3.3 GB at 3.75 TB/s (a copy
-// reaches 4.6), VALU 40 %, LDS 34 %; order 12: 1,619 -> 1,150.
+// reaches 4.6), VALU 40 %, LDS 34 %; order 12: 1,619 -> 1,150.  (Both before the momentum along
+// the axes was kept: a stage then takes 3 % and 6 % more.)
 #pragma once
 
 #include "kernels_staged.h"
